@@ -295,23 +295,20 @@ __device__ __forceinline__ void mfma_kstep(f32x16_t (&acc)[G::MI][G::NI], const 
       for (int ni = 0; ni < NI; ++ni) bfr[c ^ 1][ni] = frag<CH>(Bt, G::colblk(wcol, ni) + l32, ks + 1, lane);
     }
     copy(ks);
-    if constexpr (G::NW != 4) __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int mi = 0; mi < MI; ++mi)
 #pragma unroll
       for (int ni = 0; ni < NI; ++ni)
         acc[mi][ni] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bfr[c][ni], af[c][mi], acc[mi][ni], 0, 0, 0);
-    if constexpr (G::NW == 4) {
-      // one wave per SIMD (no second wave to cover the reads): the next slice's
-      // fragment reads go between this slice's MFMAs (scheduling groups)
-      if (ks + 1 < G::NKS) {
+    // one wave per SIMD (no second wave to cover the reads): the next slice's
+    // fragment reads go between this slice's MFMAs (scheduling groups)
+    if (ks + 1 < G::NKS) {
 #pragma unroll
-        for (int r = 0; r < MI + NI; ++r) {
-          __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-          __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-        }
-        __builtin_amdgcn_sched_group_barrier(0x008, MI * NI - (MI + NI), 0);
+      for (int r = 0; r < MI + NI; ++r) {
+        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+        __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
       }
+      __builtin_amdgcn_sched_group_barrier(0x008, MI * NI - (MI + NI), 0);
     }
     __builtin_amdgcn_sched_barrier(0);
   }
@@ -387,13 +384,14 @@ __device__ __forceinline__ void tile_epilogue(const f32x16_t (&acc)[G::MI][G::NI
   }
 }
 
-// One tile per workgroup, a ring of STAGES LDS stages: k-step kt + STAGES - 1 is in
-// flight while kt is consumed; the copies of a stage are spread over the k-slices
-// of the k-step before it.
-template <int BM, int BN, int BK, int NWM, int NWN, int STAGES, int PD, class E, bool SWIGLU>
+// One tile per workgroup of four waves, a ring of two LDS stages: k-step kt + 1 is
+// in flight while kt is consumed; the copies of a stage are spread over the
+// k-slices of the k-step before it.
+template <int BM, int BN, int NWM, int NWN, int PD, class E, bool SWIGLU>
 __global__ __launch_bounds__(64 * NWM * NWN) void gemm_bf16_kernel(const bf16_t* __restrict__ A, int64_t lda,
                                                                   const bf16_t* __restrict__ B, int64_t ldb, int M,
                                                                   int K, int d_ff, int n_bn, int group_m, E e) {
+  constexpr int BK = kBK, STAGES = 2;
   using G = TileGeom<BM, BN, BK, NWM, NWN, PD, E>;
   constexpr int PIPE = STAGES * (G::AS + G::BS);
   constexpr int ROUNDS = G::rounds_for(160 * 1024);
@@ -453,6 +451,176 @@ __global__ __launch_bounds__(64 * NWM * NWN) void gemm_bf16_kernel(const bf16_t*
     mfma_kstep<G>(acc, As + cur * G::AS, Bs + cur * G::BS, wm, wcol, lane, [&](int) {});
     cur = cur == STAGES - 1 ? 0 : cur + 1;
   }
+  __syncthreads();   // the staging area overlaps the ring
+  tile_epilogue<G, ROUNDS>(acc, smem, m0, bn, M, e, wm, wcol, tid);
+}
+
+// --------------------------------------------------------------------------- alternating 8-wave kernel
+// The 8-wave tiles in two groups of four waves, one wave of each group per SIMD,
+// half a phase apart: while one group runs the MFMAs of half a k-step, the other
+// reads its next fragments from LDS and issues copies, and a workgroup barrier
+// closes every phase.  Without the alternation both waves of a SIMD read, wait
+// and multiply at the same times, and the matrix cores idle through the reads.
+//
+// A k-step of a wave is P0 M0 P1 M1:
+//   P0  reads every B fragment and the A fragments of the wave's first MI / 2 row
+//       blocks; copies the second half of A of k-step t + 1;
+//   M0  multiplies them;
+//   P1  reads the A fragments of the other row blocks (into the same registers);
+//       copies B and the first half of A of k-step t + 2;
+//   M1  multiplies them.
+// Ring of two stages.  A phase ends with its LDS reads done, so after the barrier
+// that follows P0 (P1) of the later group a region may be written again: B and the
+// first half of A of stage t from P1(t) on, the second half from P0(t + 1) on.
+// Each P phase ends by waiting for what the next P phase reads, which was issued
+// four phases before; the copies issued in between stay in flight.
+// Bound: the matrix cores through the reads, waits and barriers of the other
+// group (MFMA busy 57-67% of the CU-busy cycles without the alternation).  Against
+// both groups in step, 32768 rows: gate|up 1320 -> 1405-1480 TFLOP/s, down (K = 14336)
+// 1206 -> 1350-1410, q|k|v 1247 -> 1320-1380, output 1105 -> 1190-1230; K = 768,
+// 65536 rows: gate|up 1033 -> 1140-1160, down 910 -> 1020-1050; bitwise the same.
+// Spreading the reads evenly over P0 and P1 (a quarter of B one phase early) and
+// leaving out the priorities measured the same within 1%.
+template <int BM, int BN, int NWM, int NWN, int PD, class E, bool SWIGLU>
+__global__ __launch_bounds__(512) void gemm_alt_kernel(const bf16_t* __restrict__ A, int64_t lda,
+                                                       const bf16_t* __restrict__ B, int64_t ldb, int M, int K,
+                                                       int d_ff, int n_bn, int group_m, E e) {
+  using G = TileGeom<BM, BN, kBK, NWM, NWN, PD, E>;
+  constexpr int MI = G::MI, NI = G::NI, MH = MI / 2, CH = G::CH, HW = G::WTM / 2;
+  constexpr int PIPE = 2 * (G::AS + G::BS);
+  constexpr int ROUNDS = G::rounds_for(160 * 1024);
+  static_assert(ROUNDS > 0, "staging");
+  constexpr int STG = G::BM / ROUNDS * G::ROW_BYTES / 16;
+  static_assert(PIPE * 16 <= 160 * 1024 && STG * 16 <= 160 * 1024, "LDS");
+  static_assert(!SWIGLU || G::REG_PAIR, "SwiGLU tiles pair gate and up in registers");
+  static_assert(NWM * NWN == 8 && NWM % 2 == 0 && MI % 2 == 0 && HW % 16 == 0 && CH == 8, "two groups of four waves");
+  constexpr int NAH = G::NA / 2, NB = G::NB;   // copies per wave: half of A, all of B
+  static_assert(G::NA % 2 == 0 && (!SWIGLU || NB % 2 == 0), "copies split evenly");
+  __shared__ __attribute__((aligned(16))) v4u smem[PIPE > STG ? PIPE : STG];
+  const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = w / NWN, wn = w % NWN;
+  const int wcol = G::wave_col(wn);
+  int bm_, bn;
+  xcd_tile((int)blockIdx.x, (M + BM - 1) / BM, n_bn, group_m, &bm_, &bn);
+  const int m0 = bm_ * BM;
+  RowGroupSrc sa, sb, su;
+  sa.init(A + (int64_t)m0 * lda, lda, w, lane);
+  if (SWIGLU) {
+    sb.init(B + (int64_t)bn * (BN / 2) * ldb, ldb, w, lane);
+    su.init(B + ((int64_t)d_ff + (int64_t)bn * (BN / 2)) * ldb, ldb, w, lane);
+  } else {
+    sb.init(B + (int64_t)bn * BN * ldb, ldb, w, lane);
+  }
+  auto copy_b = [&](int kt, int st) {
+    v4u* Bs = smem + 2 * G::AS + st * G::BS;
+#pragma unroll
+    for (int j = 0; j < NB; ++j) {
+      const int g = j * 8 + w;   // 8-row group of the B tile
+      if (SWIGLU && j >= NB / 2) su.load(kt, g - NB / 2 * 8, Bs + g * 64);
+      else sb.load(kt, g, Bs + g * 64);
+    }
+  };
+  // half h of A: of each wave's WTM rows the h-th HW
+  auto copy_a = [&](int kt, int st, int h) {
+    v4u* As = smem + st * G::AS;
+#pragma unroll
+    for (int j = 0; j < NAH; ++j) {
+      const int q = j * 8 + w;
+      const int g = q / (HW / 8) * (G::WTM / 8) + h * (HW / 8) + q % (HW / 8);
+      sa.load(kt, g, As + g * 64);
+    }
+  };
+
+  f32x16_t acc[MI][NI];
+#pragma unroll
+  for (int mi = 0; mi < MI; ++mi)
+#pragma unroll
+    for (int ni = 0; ni < NI; ++ni)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) acc[mi][ni][i] = 0.f;
+  bf16x8_t af[MH][G::NKS], bfr[NI][G::NKS];
+  auto read_b = [&](int st) {
+    const v4u* Bt = smem + 2 * G::AS + st * G::BS;
+#pragma unroll
+    for (int ks = 0; ks < G::NKS; ++ks)
+#pragma unroll
+      for (int ni = 0; ni < NI; ++ni) bfr[ni][ks] = frag<CH>(Bt, G::colblk(wcol, ni) + l32, ks, lane);
+  };
+  auto read_a = [&](int st, int h) {
+    const v4u* At = smem + st * G::AS;
+#pragma unroll
+    for (int ks = 0; ks < G::NKS; ++ks)
+#pragma unroll
+      for (int mi = 0; mi < MH; ++mi) af[mi][ks] = frag<CH>(At, wm * G::WTM + h * HW + mi * 32 + l32, ks, lane);
+  };
+  auto mma = [&](auto H) {
+    constexpr int h = decltype(H)::value;
+    __builtin_amdgcn_s_setprio(1);
+#pragma unroll
+    for (int ks = 0; ks < G::NKS; ++ks)
+#pragma unroll
+      for (int mi = 0; mi < MH; ++mi)
+#pragma unroll
+        for (int ni = 0; ni < NI; ++ni)
+          acc[h * MH + mi][ni] =
+              __builtin_amdgcn_mfma_f32_32x32x16_bf16(bfr[ni][ks], af[mi][ks], acc[h * MH + mi][ni], 0, 0, 0);
+    __builtin_amdgcn_s_setprio(0);
+  };
+  typedef std::integral_constant<int, 0> H0;
+  typedef std::integral_constant<int, 1> H1;
+
+  const int nk = K / kBK;
+  copy_b(0, 0);
+  copy_a(0, 0, 0);
+  copy_a(0, 0, 1);
+  if (nk > 1) {
+    copy_b(1, 1);
+    copy_a(1, 1, 0);
+    wait_vmem_le<NB + 2 * NAH>();   // B and the first half of A of k-step 0
+  } else {
+    wait_vmem();
+  }
+  phase_barrier();
+  if (w >= 4) phase_barrier();   // the second group runs one phase behind
+  int t = 0;
+  for (; t < nk - 2; ++t) {
+    const int st = t & 1;
+    read_b(st);
+    read_a(st, 0);
+    copy_a(t + 1, st ^ 1, 1);
+    wait_reads_and_copies<NB + 2 * NAH>();   // second half of A of k-step t
+    phase_barrier();
+    mma(H0{});
+    phase_barrier();
+    read_a(st, 1);
+    copy_b(t + 2, st);
+    copy_a(t + 2, st, 0);
+    wait_reads_and_copies<NB + 2 * NAH>();   // B and the first half of A of k-step t + 1
+    phase_barrier();
+    mma(H1{});
+    phase_barrier();
+  }
+  for (; t < nk; ++t) {   // the last two k-steps: at most one half of A is left to copy
+    const int st = t & 1;
+    read_b(st);
+    read_a(st, 0);
+    if (t + 1 < nk) {
+      copy_a(t + 1, st ^ 1, 1);
+      wait_reads_and_copies<NB + 2 * NAH>();
+    } else {
+      wait_reads_and_copies<0>();
+    }
+    phase_barrier();
+    mma(H0{});
+    phase_barrier();
+    read_a(st, 1);
+    wait_reads_and_copies<NAH>();
+    phase_barrier();
+    mma(H1{});
+    phase_barrier();
+  }
+  if (w < 4) phase_barrier();
   __syncthreads();   // the staging area overlaps the ring
   tile_epilogue<G, ROUNDS>(acc, smem, m0, bn, M, e, wm, wcol, tid);
 }
@@ -524,9 +692,6 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(const float* __restrict__
 }
 
 // --------------------------------------------------------------------------- dispatch
-// Tile choice (measured on MI355X over the decoder's projection shapes): a
-// 256x256 tile on 8 waves (2x4, 128x64 per wave) wherever it divides N and
-// yields at least half a wave of tiles; otherwise 128x128 on 4 waves.
 static int cu_count() {
   static int n = 0;
   if (n == 0) {
@@ -539,7 +704,9 @@ static int cu_count() {
   return n;
 }
 
-static void pick_tile(const GemmArgs& a, bool swiglu, int* bm, int* bn_, int* bk, int* waves, int* stages) {
+enum class Tile { k256x256, k256x192, k128x128 };
+
+static Tile pick_tile(const GemmArgs& a, bool swiglu) {
   const int ncu = cu_count();
   const int64_t nm = (a.M + 255) / 256;
   const bool fits256 = swiglu ? (a.d_ff % 128 == 0) : (a.N % 256 == 0);
@@ -548,46 +715,42 @@ static void pick_tile(const GemmArgs& a, bool swiglu, int* bm, int* bn_, int* bk
   const bool fits192 = !swiglu && a.N % 192 == 0 && a.epi != Epi::kStoreRope;
   const int64_t tiles256 = fits256 ? nm * (a.N / 256) : 0, tiles192 = fits192 ? nm * (a.N / 192) : 0;
   // fewer than half a wave of large tiles on the CUs (small M, e.g. window rows): 128x128 tiles
-  if (a.K % 64 == 0 && std::max(tiles256, tiles192) >= ncu / 2) {
-    // the 256-row tile whose last round of workgroups wastes least: cost = rounds x tile area
-    const int64_t c256 = fits256 ? (tiles256 + ncu - 1) / ncu * 256 : INT64_MAX;
-    const int64_t c192 = fits192 ? (tiles192 + ncu - 1) / ncu * 192 : INT64_MAX;
-    *bm = 256; *bn_ = c192 < c256 ? 192 : 256; *bk = 64; *waves = 8; *stages = 2;
-    return;
-  }
-  *bm = 128; *bn_ = 128; *bk = 64; *waves = 4; *stages = 2;
+  if (std::max(tiles256, tiles192) < ncu / 2) return Tile::k128x128;
+  // the 256-row tile whose last round of workgroups wastes least: cost = rounds x tile area
+  const int64_t c256 = fits256 ? (tiles256 + ncu - 1) / ncu * 256 : INT64_MAX;
+  const int64_t c192 = fits192 ? (tiles192 + ncu - 1) / ncu * 192 : INT64_MAX;
+  return c192 < c256 ? Tile::k256x192 : Tile::k256x256;
 }
 
-template <int BM, int BN, int BK, int ST, int PD, class E, bool SWIGLU, int NWM, int NWN>
+template <int BM, int BN, int NWM, int NWN, int PD, class E, bool SWIGLU>
 static void go_pd(const GemmArgs& a, const E& e, hipStream_t s) {
   const int nbn = SWIGLU ? a.d_ff / (BN / 2) : a.N / BN;
   const int nbm = (a.M + BM - 1) / BM;
   // tile-rows per L2 group: 4 for the long-K projections of the 8B-scale models
   // (1-2% faster than 8 on q|k|v, output and down at 32768 rows, equal on
   // gate|up), 8 for short K
-  const int group_m = a.group_m > 0 ? a.group_m : (a.K >= 4096 ? 4 : 8);
-  gemm_bf16_kernel<BM, BN, BK, NWM, NWN, ST, PD, E, SWIGLU><<<nbm * nbn, 64 * NWM * NWN, 0, s>>>(
-      (const bf16_t*)a.A, a.lda, (const bf16_t*)a.B, a.ldb, a.M, a.K, a.d_ff, nbn, group_m, e);
+  const int group_m = a.K >= 4096 ? 4 : 8;
+  const bf16_t *A = (const bf16_t*)a.A, *B = (const bf16_t*)a.B;
+  if constexpr (NWM * NWN == 8)
+    gemm_alt_kernel<BM, BN, NWM, NWN, PD, E, SWIGLU>
+        <<<nbm * nbn, 512, 0, s>>>(A, a.lda, B, a.ldb, a.M, a.K, a.d_ff, nbn, group_m, e);
+  else
+    gemm_bf16_kernel<BM, BN, NWM, NWN, PD, E, SWIGLU>
+        <<<nbm * nbn, 64 * NWM * NWN, 0, s>>>(A, a.lda, B, a.ldb, a.M, a.K, a.d_ff, nbn, group_m, e);
 }
 
 // the pair distance each epilogue needs (plain layout when it pairs nothing)
-template <int BM, int BN, int BK, int ST, class E, bool SWIGLU, int NWM = 2, int NWN = 2>
+template <int BM, int BN, class E, bool SWIGLU, int NWM, int NWN>
 static hipError_t go_bf16(const GemmArgs& a, const E& e, hipStream_t s) {
-  constexpr int WTN = BN / NWN;
-  if constexpr (WTN != 64 && WTN != 128) {   // three column blocks per wave: pairs via the staged tile
-    if constexpr (SWIGLU) {
-      return hipErrorInvalidValue;   // SwiGLU needs the paired layout
-    } else {
-      if (E::kPaired && BN % a.head_dim != 0) return hipErrorInvalidValue;   // rotary pairs inside the tile
-      go_pd<BM, BN, BK, ST, 32, E, SWIGLU, NWM, NWN>(a, e, s);
-    }
-  } else if constexpr (!E::kPaired) {
-    go_pd<BM, BN, BK, ST, 32, E, SWIGLU, NWM, NWN>(a, e, s);
+  if constexpr (!E::kPaired) {
+    go_pd<BM, BN, NWM, NWN, 32, E, SWIGLU>(a, e, s);
+  } else if constexpr (BN % 128 != 0) {
+    return hipErrorInvalidValue;   // three column blocks per wave: no pairs in registers
   } else if constexpr (SWIGLU) {
-    go_pd<BM, BN, BK, ST, BN / 2, E, SWIGLU, NWM, NWN>(a, e, s);
+    go_pd<BM, BN, NWM, NWN, BN / 2, E, SWIGLU>(a, e, s);
   } else {
-    if (a.head_dim == 64) go_pd<BM, BN, BK, ST, 32, E, SWIGLU, NWM, NWN>(a, e, s);
-    else if (a.head_dim == 128) go_pd<BM, BN, BK, ST, 64, E, SWIGLU, NWM, NWN>(a, e, s);
+    if (a.head_dim == 64) go_pd<BM, BN, NWM, NWN, 32, E, SWIGLU>(a, e, s);
+    else if (a.head_dim == 128) go_pd<BM, BN, NWM, NWN, 64, E, SWIGLU>(a, e, s);
     else return hipErrorInvalidValue;
   }
   return hipGetLastError();
@@ -596,23 +759,11 @@ static hipError_t go_bf16(const GemmArgs& a, const E& e, hipStream_t s) {
 template <class E, bool SWIGLU>
 static hipError_t go(const GemmArgs& a, bool bf16, const E& e, hipStream_t s) {
   if (bf16) {
-    int bm, bn, bk, waves, st;
-    pick_tile(a, SWIGLU, &bm, &bn, &bk, &waves, &st);
-    if (a.tile_m) {
-      bm = a.tile_m; bn = a.tile_n; bk = a.tile_k ? a.tile_k : 64; waves = a.tile_waves ? a.tile_waves : 4;
-      st = a.tile_stages ? a.tile_stages : 2;
+    switch (pick_tile(a, SWIGLU)) {
+      case Tile::k256x256: return go_bf16<256, 256, E, SWIGLU, 2, 4>(a, e, s);
+      case Tile::k256x192: return go_bf16<256, 192, E, SWIGLU, 4, 2>(a, e, s);
+      case Tile::k128x128: return go_bf16<128, 128, E, SWIGLU, 2, 2>(a, e, s);
     }
-#define RK_TILE(BM_, BN_, BK_, W_, ST_, NWM_, NWN_)                                     \
-  if (bm == BM_ && bn == BN_ && bk == BK_ && waves == W_ && st == ST_)                  \
-    return go_bf16<BM_, BN_, BK_, ST_, E, SWIGLU, NWM_, NWN_>(a, e, s);
-    // each wave: two 32-column blocks (BN = 64 NWN) or three (BN = 96 NWN, not SwiGLU)
-    RK_TILE(256, 256, 64, 8, 2, 2, 4)
-    RK_TILE(256, 192, 64, 8, 2, 4, 2)
-    RK_TILE(256, 256, 32, 8, 3, 2, 4)
-    RK_TILE(256, 256, 32, 8, 4, 2, 4)
-    RK_TILE(128, 128, 64, 4, 2, 2, 2)
-    RK_TILE(128, 128, 64, 4, 3, 2, 2)
-#undef RK_TILE
     return hipErrorInvalidValue;
   } else {
     const int nbn = SWIGLU ? a.d_ff / 64 : a.N / 128;

@@ -91,6 +91,52 @@ struct TileSrcT {
 };
 typedef TileSrcT<kBK, 4> TileSrc;
 
+// Copies of single 8-row groups of a 64-wide k-step (128-byte rows, CH = 8): one
+// wave instruction fills the 64 slots of group g, rows 8 g .. 8 g + 7 from the
+// tile's first row.  The groups a wave copies all have the parity of its index w,
+// so the swizzle of its lanes is fixed at init.
+struct RowGroupSrc {
+  i32x4_t rsrc;
+  uint32_t voff;
+  int32_t group_bytes;
+  __device__ __forceinline__ void init(const bf16_t* rows0, int64_t ld, int w, int lane) {
+    const int r = (w & 1) * 8 + lane / 8;
+    const uint64_t base = (uint64_t)rows0;
+    rsrc[0] = __builtin_amdgcn_readfirstlane((int32_t)(uint32_t)base);
+    rsrc[1] = __builtin_amdgcn_readfirstlane((int32_t)(uint32_t)(base >> 32));
+    rsrc[2] = -1;            // no range limit: callers keep every row readable
+    rsrc[3] = 0x00020000;    // raw buffer, 32-bit data format (gfx9 word 3)
+    voff = (uint32_t)(lane / 8 * ld * 2 + ((lane % 8) ^ swz<8>(r)) * 16);
+    group_bytes = __builtin_amdgcn_readfirstlane((int32_t)(8 * ld * 2));
+  }
+  // group g (parity of w) of k-step kt to the 64 slots at dst
+  __device__ __forceinline__ void load(int kt, int g, v4u* dst) const {
+    const uint32_t lds = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(__attribute__((address_space(3))) v4u*)dst);
+    const int32_t soff = __builtin_amdgcn_readfirstlane(kt * (kBK * 2) + g * group_bytes);
+    asm volatile("s_nop 0\n\tbuffer_load_dwordx4 %0, %1, %2 offen lds"
+                 :
+                 : "v"(voff), "s"(rsrc), "s"(soff), "{m0}"(lds)
+                 : "memory");
+  }
+};
+
+// Workgroup barrier without a wait of its own; nothing is moved across it.
+__device__ __forceinline__ void phase_barrier() {
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_sched_barrier(0);
+  __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_sched_barrier(0);
+  asm volatile("" ::: "memory");
+}
+
+// s_waitcnt vmcnt(N) lgkmcnt(0): at most N copies in flight, every LDS read done
+template <int N>
+__device__ __forceinline__ void wait_reads_and_copies() {
+  static_assert(N >= 0 && N < 64, "vmcnt field");
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_waitcnt(0x0070 | (N & 15) | ((N >> 4) << 14));
+}
+
 // One 32x16 (or 16x32) bf16 fragment of row `row`, k-slice ks, from a swizzled tile.
 template <int CH = 8>
 __device__ __forceinline__ bf16x8_t frag(const v4u* tile, int row, int ks, int lane) {

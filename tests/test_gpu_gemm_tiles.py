@@ -1,0 +1,107 @@
+"""The projection GEMMs at the edges of their tiles, through one decoder block.
+
+rk_reference_forward of a two-layer model leaves the input of block 1, which is
+the output of block 0: the four projections with their epilogues (rotary,
+residual, SwiGLU).  Reference: the same block in float64 with plain torch
+operations, from the same bf16 weights.
+
+Tolerance: the block rounds x, q|k|v, the attention output, the second x and the
+feed-forward activations to bf16 (relative 2^-9 each, uniform, so rms 2^-9 /
+sqrt(3) = 1.1e-3); five such roundings in a row give a relative 2-norm of about
+sqrt(5) * 1.1e-3 = 2.5e-3 of the block's update, and a single element stays within
+five standard deviations of a few times that.  A misplaced tile, row or k-step is
+an error of the update's own size.
+"""
+from __future__ import annotations
+
+import math
+
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+class Shape:
+    def __init__(self, d, heads, kv_heads, head_dim, d_ff, vocab=128):
+        self.n_layers, self.d_model, self.n_heads, self.n_kv_heads = 2, d, heads, kv_heads
+        self.head_dim, self.d_ff, self.vocab = head_dim, d_ff, vocab
+        self.rope_theta, self.rms_eps, self.dtype = 1.0e4, 1.0e-5, "bf16"
+
+
+def block(m, w, h, lengths):
+    """One decoder block in float64."""
+    import torch
+    f = lambda k: w[k][0].double()
+
+    def norm(x, g):
+        return x * torch.rsqrt(x.square().mean(-1, keepdim=True) + m.rms_eps) * g
+
+    qc, kc = m.n_heads * m.head_dim, m.n_kv_heads * m.head_dim
+    y = norm(h, f("attn_norm")) @ f("w_qkv").t()
+    half = m.head_dim // 2
+    pos = torch.cat([torch.arange(t, device=h.device) for t in lengths]).double()
+    freq = m.rope_theta ** (-torch.arange(half, device=h.device).double() * 2 / m.head_dim)
+    c, s = torch.cos(pos[:, None, None] * freq), torch.sin(pos[:, None, None] * freq)
+
+    def rope(x):
+        x = x.view(x.shape[0], -1, m.head_dim)
+        a, b = x[..., :half], x[..., half:]
+        return torch.cat([a * c - b * s, b * c + a * s], -1)
+
+    q, k, v = rope(y[:, :qc]), rope(y[:, qc:qc + kc]), y[:, qc + kc:].reshape(len(h), -1, m.head_dim)
+    out, o, grp = torch.empty_like(q), 0, m.n_heads // m.n_kv_heads
+    for t in lengths:
+        mask = torch.ones(t, t, device=h.device, dtype=torch.bool).triu(1)
+        for g in range(m.n_heads):
+            sc = (q[o:o + t, g] @ k[o:o + t, g // grp].t()) / math.sqrt(m.head_dim)
+            out[o:o + t, g] = torch.softmax(sc.masked_fill(mask, -math.inf), -1) @ v[o:o + t, g // grp]
+        o += t
+    h = h + out.reshape(len(h), -1) @ f("w_o").t()
+    gu = norm(h, f("mlp_norm")) @ f("w_gate_up").t()
+    return h + (torch.nn.functional.silu(gu[:, :m.d_ff]) * gu[:, m.d_ff:]) @ f("w_down").t()
+
+
+def check_block(m, lengths, tol=7.5e-3, big=0.06):
+    import torch
+    import paper_2608_08684_amd as rk
+    g = torch.Generator(device="cuda").manual_seed(5)
+    mat = lambda r, c, s=0.05: torch.empty(r, c, device="cuda", dtype=torch.bfloat16).normal_(0, s, generator=g)
+    gain = lambda: 1.0 + 0.2 * torch.randn(m.d_model, device="cuda", generator=g)
+    qkv, att = (m.n_heads + 2 * m.n_kv_heads) * m.head_dim, m.n_heads * m.head_dim
+    L = range(m.n_layers)
+    w = {"tok_emb": mat(m.vocab, m.d_model, 1.0), "lm_head": mat(m.vocab, m.d_model), "final_norm": gain(),
+         "w_qkv": [mat(qkv, m.d_model) for _ in L], "w_o": [mat(m.d_model, att) for _ in L],
+         "w_gate_up": [mat(2 * m.d_ff, m.d_model) for _ in L], "w_down": [mat(m.d_model, m.d_ff) for _ in L],
+         "attn_norm": [gain() for _ in L], "mlp_norm": [gain() for _ in L]}
+    offs = [0]
+    for t in lengths:
+        offs.append(offs[-1] + t)
+    rows = offs[-1]
+    tok = torch.randint(0, m.vocab, (rows,), device="cuda", generator=g, dtype=torch.int32)
+    model, batch = rk.Model(m, w), rk.Batch(tok, offs)
+    # the buffers' tails hold NaN: padding rows that reach a result show
+    state = torch.full((model.clean_state_size(rows),), 0xFF, dtype=torch.uint8, device="cuda")
+    ws = torch.full((model.workspace_size(rows, 1, 0),), 0xFF, dtype=torch.uint8, device="cuda")
+    model.reference_forward(batch, state, ws)
+    torch.cuda.synchronize()
+    h = state[:m.n_layers * rows * m.d_model * 4].view(torch.float32).view(m.n_layers, rows, m.d_model)
+    h0 = w["tok_emb"][tok.long()].double()
+    assert torch.equal(h[0].double(), h0)
+    want = block(m, w, h0, lengths) - h0
+    got = h[1].double() - h0
+    rel = ((got - want).norm() / want.norm()).item()
+    worst = ((got - want).abs().max() / want.square().mean().sqrt()).item()
+    print(f"rows {rows}: update off by {rel:.2e} (2-norm), {worst:.2e} of its rms at most")
+    assert rel < tol and worst < big
+
+
+# large M: the 8-wave tiles, with one, two, three and four k-steps and ragged last tile rows
+@pytest.mark.parametrize("m, lengths", [
+    (Shape(256, 4, 4, 64, 64), [512] * 63 + [300]),
+    (Shape(256, 2, 2, 128, 128), [512] * 63 + [511]),
+    (Shape(256, 4, 2, 64, 192), [512] * 64),
+    (Shape(768, 12, 12, 64, 384), [512] * 22 + [257]),    # 192-wide residual tiles
+    (Shape(512, 4, 1, 128, 320), [700] * 23 + [1]),
+], ids=["k64", "k128", "k192", "n192", "k320"])
+def test_large_tiles(m, lengths):
+    check_block(m, lengths)
