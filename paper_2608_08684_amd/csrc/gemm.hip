@@ -4,12 +4,11 @@
 //   output / down     -> residual add into the fp32 stream,
 //   gate|up           -> SwiGLU (silu(gate) * up), written as one [M, d_ff] tile,
 //   LM head (unfused) -> plain fp32 logits.
-// bf16 path: BM x BN block tile (256x256 or 256x192 on 8 waves, whichever wastes
-// less of the last round of workgroups; 128x128 on 4 for small M),
-// v_mfma_f32_32x32x16_bf16, K-steps streamed global -> LDS by buffer loads into a
-// ring of LDS stages (see mfma_tile.h).  The finished tile leaves through LDS so
-// the global accesses are whole rows; a rotary pair j, j + d_h/2 or a gate/up pair
-// always lies inside one tile.
+// bf16 path: BM x BN block tiles (256 rows on 8 waves for many rows, 32 or 64 rows
+// with a deep ring for few; pick_tile), v_mfma_f32_32x32x16_bf16,
+// K-steps streamed global -> LDS by buffer loads into rings of LDS stages (see
+// mfma_tile.h).  The finished tile leaves through LDS so the global accesses are
+// whole rows; a rotary pair j, j + d_h/2 or a gate/up pair always lies inside one tile.
 // fp32 path: a VALU kernel with the same epilogues (64x128 tile), staged 64 rows
 // at a time.
 #include "mfma_tile.h"
@@ -54,6 +53,11 @@ __device__ __forceinline__ void copy16(bf16_t* dst, const bf16_t* src) {
 }
 
 // --------------------------------------------------------------------------- epilogues
+// The two runs of columns that a split-K tile holds: rows of B (b0 .., b1 ..) and
+// the output columns they end in.
+struct ColRuns {
+  int b0, b1, o0, o1;
+};
 // Called per (row, 8 consecutive output columns starting at c0) with cs = the
 // staged fp32 row of a BN-wide tile.  out_cols(BN) = output columns per tile.
 template <typename O>
@@ -110,6 +114,18 @@ struct EpiRope {
     o1 = make_float4(fmaf(x.x, t01.y, y.x * t01.x) * sc, fmaf(x.y, t01.w, y.y * t01.z) * sc,
                      fmaf(x.z, t23.y, y.z * t23.x) * sc, fmaf(x.w, t23.w, y.w * t23.z) * sc);
   }
+  // HB columns of the first half of a head and their partners (q|k|v width: whole heads)
+  template <int HB>
+  __device__ __forceinline__ ColRuns runs(int bn, int) const {
+    const int half = head_dim >> 1, per = half / HB, c = bn / per * head_dim + bn % per * HB;
+    return {c, c + half, c, c + half};
+  }
+  __device__ __forceinline__ void put(int row, const ColRuns& cr, int c, float4 x, float4 y) const {
+    float4 p, q;
+    pair<1>(row, 0, cr.o0 + c, x, y, p, q);
+    store4(out + (int64_t)row * ldo + cr.o0 + c, p);
+    store4(out + (int64_t)row * ldo + cr.o1 + c, q);
+  }
 };
 
 struct EpiResidual {
@@ -117,6 +133,16 @@ struct EpiResidual {
   static constexpr bool kPaired = false;
   float* out; int64_t ldo; const float* res; int64_t ldr;
   using stage_t = float;
+  template <int HB>
+  __device__ __forceinline__ ColRuns runs(int bn, int) const {
+    return {bn * 2 * HB, bn * 2 * HB + HB, bn * 2 * HB, bn * 2 * HB + HB};
+  }
+  __device__ __forceinline__ void put(int row, const ColRuns& cr, int c, float4 x, float4 y) const {
+    const float4 a = *reinterpret_cast<const float4*>(res + (int64_t)row * ldr + cr.o0 + c);
+    const float4 b = *reinterpret_cast<const float4*>(res + (int64_t)row * ldr + cr.o1 + c);
+    store4(out + (int64_t)row * ldo + cr.o0 + c, make_float4(a.x + x.x, a.y + x.y, a.z + x.z, a.w + x.w));
+    store4(out + (int64_t)row * ldo + cr.o1 + c, make_float4(b.x + y.x, b.y + y.y, b.z + y.z, b.w + y.w));
+  }
   template <int BN>
   __device__ void apply(int row, int bn, int c0, const float* cs) const {
     const int64_t n = (int64_t)bn * BN + c0;
@@ -145,6 +171,14 @@ struct EpiSwiGLU {
   __device__ __forceinline__ void pair(int, int, int, float4 g, float4 u, float4& o0, float4&) const {
     o0 = make_float4(silu_mul(g.x, u.x), silu_mul(g.y, u.y), silu_mul(g.z, u.z), silu_mul(g.w, u.w));
   }
+  template <int HB>
+  __device__ __forceinline__ ColRuns runs(int bn, int d_ff) const {
+    return {bn * HB, d_ff + bn * HB, bn * HB, bn * HB};
+  }
+  __device__ __forceinline__ void put(int row, const ColRuns& cr, int c, float4 x, float4 y) const {
+    store4(out + (int64_t)row * ldo + cr.o0 + c, make_float4(silu_mul(x.x, y.x), silu_mul(x.y, y.y),
+                                                             silu_mul(x.z, y.z), silu_mul(x.w, y.w)));
+  }
   template <int BN>
   __device__ void apply(int row, int bn, int c0, const float* cs) const {
     // silu(g) = g / (1 + e^-g) with the hardware exp2 and reciprocal (about 1 ulp
@@ -165,6 +199,14 @@ struct EpiStoreF32 {
   static constexpr bool kPaired = false;
   float* out; int64_t ldo;
   using stage_t = float;
+  template <int HB>
+  __device__ __forceinline__ ColRuns runs(int bn, int) const {
+    return {bn * 2 * HB, bn * 2 * HB + HB, bn * 2 * HB, bn * 2 * HB + HB};
+  }
+  __device__ __forceinline__ void put(int row, const ColRuns& cr, int c, float4 x, float4 y) const {
+    store4(out + (int64_t)row * ldo + cr.o0 + c, x);
+    store4(out + (int64_t)row * ldo + cr.o1 + c, y);
+  }
   template <int BN>
   __device__ void apply(int row, int bn, int c0, const float* cs) const {
     store8(out + (int64_t)row * ldo + (int64_t)bn * BN + c0, cs + c0);
@@ -242,78 +284,6 @@ struct TileGeom {
   }
 };
 
-// The global -> LDS copy sources of one tile: A rows m0.., B rows (or gate and up
-// rows) of column block bn.
-template <class G, bool SWIGLU>
-struct TileCopies {
-  TileSrcT<G::BK, G::NW> sa, sb, su;
-  __device__ __forceinline__ void init(const bf16_t* A, int64_t lda, const bf16_t* B, int64_t ldb, int d_ff, int m0,
-                                       int bn, int w, int lane) {
-    sa.init(A + (int64_t)m0 * lda, lda, w, lane);
-    if (SWIGLU) {
-      sb.init(B + (int64_t)bn * (G::BN / 2) * ldb, ldb, w, lane);
-      su.init(B + ((int64_t)d_ff + (int64_t)bn * (G::BN / 2)) * ldb, ldb, w, lane);
-    } else {
-      sb.init(B + (int64_t)bn * G::BN * ldb, ldb, w, lane);
-    }
-  }
-  // copy j (of NL) of k-step kt into the stage whose A tile is at As and B tile at Bs
-  __device__ __forceinline__ void issue_one(int kt, v4u* As, v4u* Bs, int j, int w) const {
-    if (j < G::NA) {
-      sa.load_round(kt, j, As, w);
-    } else if (SWIGLU) {
-      const int jb = j - G::NA;
-      if (jb < G::NB / 2) sb.load_round(kt, jb, Bs, w);
-      else su.load_round(kt, jb - G::NB / 2, Bs + (G::BN / 2) * G::CH, w);
-    } else {
-      sb.load_round(kt, j - G::NA, Bs, w);
-    }
-  }
-};
-
-// One k-step from the stage (At, Bt): fragments double-buffered in registers; the
-// LDS reads of k-slice ks + 1 and this k-step's share of the next copies
-// (copy(ks)) are issued ahead of the MFMAs of slice ks.
-template <class G, class Copy>
-__device__ __forceinline__ void mfma_kstep(f32x16_t (&acc)[G::MI][G::NI], const v4u* At, const v4u* Bt, int wm,
-                                           int wcol, int lane, const Copy& copy) {
-  constexpr int MI = G::MI, NI = G::NI, CH = G::CH;
-  const int l32 = lane & 31;
-  bf16x8_t af[2][MI], bfr[2][NI];
-#pragma unroll
-  for (int mi = 0; mi < MI; ++mi) af[0][mi] = frag<CH>(At, wm * G::WTM + mi * 32 + l32, 0, lane);
-#pragma unroll
-  for (int ni = 0; ni < NI; ++ni) bfr[0][ni] = frag<CH>(Bt, G::colblk(wcol, ni) + l32, 0, lane);
-  __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-  for (int ks = 0; ks < G::NKS; ++ks) {
-    const int c = ks & 1;
-    if (ks + 1 < G::NKS) {
-#pragma unroll
-      for (int mi = 0; mi < MI; ++mi) af[c ^ 1][mi] = frag<CH>(At, wm * G::WTM + mi * 32 + l32, ks + 1, lane);
-#pragma unroll
-      for (int ni = 0; ni < NI; ++ni) bfr[c ^ 1][ni] = frag<CH>(Bt, G::colblk(wcol, ni) + l32, ks + 1, lane);
-    }
-    copy(ks);
-#pragma unroll
-    for (int mi = 0; mi < MI; ++mi)
-#pragma unroll
-      for (int ni = 0; ni < NI; ++ni)
-        acc[mi][ni] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bfr[c][ni], af[c][mi], acc[mi][ni], 0, 0, 0);
-    // one wave per SIMD (no second wave to cover the reads): the next slice's
-    // fragment reads go between this slice's MFMAs (scheduling groups)
-    if (ks + 1 < G::NKS) {
-#pragma unroll
-      for (int r = 0; r < MI + NI; ++r) {
-        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-        __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-      }
-      __builtin_amdgcn_sched_group_barrier(0x008, MI * NI - (MI + NI), 0);
-    }
-    __builtin_amdgcn_sched_barrier(0);
-  }
-}
-
 // Epilogue of one tile, staged in ROUNDS passes through the LDS at `stage`.  The
 // MFMAs take B as the first operand, so acc[mi][ni] is the transposed 32x32 block:
 // lane l holds row l % 32 and, in elements 4g..4g+3, the four consecutive columns
@@ -384,77 +354,6 @@ __device__ __forceinline__ void tile_epilogue(const f32x16_t (&acc)[G::MI][G::NI
   }
 }
 
-// One tile per workgroup of four waves, a ring of two LDS stages: k-step kt + 1 is
-// in flight while kt is consumed; the copies of a stage are spread over the
-// k-slices of the k-step before it.
-template <int BM, int BN, int NWM, int NWN, int PD, class E, bool SWIGLU>
-__global__ __launch_bounds__(64 * NWM * NWN) void gemm_bf16_kernel(const bf16_t* __restrict__ A, int64_t lda,
-                                                                  const bf16_t* __restrict__ B, int64_t ldb, int M,
-                                                                  int K, int d_ff, int n_bn, int group_m, E e) {
-  constexpr int BK = kBK, STAGES = 2;
-  using G = TileGeom<BM, BN, BK, NWM, NWN, PD, E>;
-  constexpr int PIPE = STAGES * (G::AS + G::BS);
-  constexpr int ROUNDS = G::rounds_for(160 * 1024);
-  static_assert(ROUNDS > 0, "staging");
-  constexpr int STG = G::BM / ROUNDS * G::ROW_BYTES / 16;
-  static_assert(PIPE * 16 <= 160 * 1024 && STG * 16 <= 160 * 1024, "LDS");
-  static_assert(!SWIGLU || G::REG_PAIR, "SwiGLU tiles pair gate and up in registers");
-  constexpr int NL = G::NL;
-  static_assert(STAGES >= 2 && (STAGES - 2) * NL < 16, "ring depth");
-  __shared__ __attribute__((aligned(16))) v4u smem[PIPE > STG ? PIPE : STG];
-  v4u* As = smem;
-  v4u* Bs = smem + STAGES * G::AS;
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-  const int wm = w / NWN, wn = w % NWN;
-  const int wcol = G::wave_col(wn);
-  int bm_, bn;
-  xcd_tile((int)blockIdx.x, (M + BM - 1) / BM, n_bn, group_m, &bm_, &bn);
-  const int m0 = bm_ * BM;
-  TileCopies<G, SWIGLU> src;
-  src.init(A, lda, B, ldb, d_ff, m0, bn, w, lane);
-  constexpr int PER = (NL + 1) / 2;   // copies issued per k-slice: over the first two slices
-
-  f32x16_t acc[G::MI][G::NI];
-#pragma unroll
-  for (int mi = 0; mi < G::MI; ++mi)
-#pragma unroll
-    for (int ni = 0; ni < G::NI; ++ni)
-#pragma unroll
-      for (int i = 0; i < 16; ++i) acc[mi][ni][i] = 0.f;
-
-  const int nk = K / BK;
-#pragma unroll
-  for (int p = 0; p < STAGES - 1; ++p)
-    if (p < nk)
-#pragma unroll
-      for (int j = 0; j < NL; ++j) src.issue_one(p, As + p * G::AS, Bs + p * G::BS, j, w);
-  int cur = 0, nxt = STAGES - 1;
-  // The copying k-steps and the last STAGES - 1 (which copy nothing) run as two
-  // loops, so each k-slice's reads, copies and MFMAs form one basic block that
-  // the compiler schedules as a whole (+2-3% at the Llama-3-8B shapes against a
-  // per-k-step test of whether to copy).
-  int kt = 0;
-  for (; kt + STAGES - 1 < nk; ++kt) {   // steady state: each k-step copies k-step kt + STAGES - 1
-    wait_vmem_le<(STAGES - 2) * NL>();
-    __syncthreads();   // k-step kt is in LDS for every wave; the slot of kt - 1 is free
-    mfma_kstep<G>(acc, As + cur * G::AS, Bs + cur * G::BS, wm, wcol, lane, [&](int ks) {
-#pragma unroll
-      for (int j = ks * PER; j < (ks + 1) * PER; ++j)
-        if (j < NL) src.issue_one(kt + STAGES - 1, As + nxt * G::AS, Bs + nxt * G::BS, j, w);
-    });
-    cur = cur == STAGES - 1 ? 0 : cur + 1;
-    nxt = nxt == STAGES - 1 ? 0 : nxt + 1;
-  }
-  for (; kt < nk; ++kt) {   // the last STAGES - 1 k-steps copy nothing
-    wait_vmem();
-    __syncthreads();
-    mfma_kstep<G>(acc, As + cur * G::AS, Bs + cur * G::BS, wm, wcol, lane, [&](int) {});
-    cur = cur == STAGES - 1 ? 0 : cur + 1;
-  }
-  __syncthreads();   // the staging area overlaps the ring
-  tile_epilogue<G, ROUNDS>(acc, smem, m0, bn, M, e, wm, wcol, tid);
-}
-
 // --------------------------------------------------------------------------- alternating 8-wave kernel
 // The 8-wave tiles in two groups of four waves, one wave of each group per SIMD,
 // half a phase apart: while one group runs the MFMAs of half a k-step, the other
@@ -512,23 +411,24 @@ __global__ __launch_bounds__(512) void gemm_alt_kernel(const bf16_t* __restrict_
   } else {
     sb.init(B + (int64_t)bn * BN * ldb, ldb, w, lane);
   }
+  const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) v4u*)smem;
   auto copy_b = [&](int kt, int st) {
-    v4u* Bs = smem + 2 * G::AS + st * G::BS;
+    const uint32_t Bs = lds0 + (2 * G::AS + st * G::BS) * 16;
 #pragma unroll
     for (int j = 0; j < NB; ++j) {
       const int g = j * 8 + w;   // 8-row group of the B tile
-      if (SWIGLU && j >= NB / 2) su.load(kt, g - NB / 2 * 8, Bs + g * 64);
-      else sb.load(kt, g, Bs + g * 64);
+      if (SWIGLU && j >= NB / 2) su.load_at(kt, g - NB / 2 * 8, Bs + g * 1024);
+      else sb.load_at(kt, g, Bs + g * 1024);
     }
   };
   // half h of A: of each wave's WTM rows the h-th HW
   auto copy_a = [&](int kt, int st, int h) {
-    v4u* As = smem + st * G::AS;
+    const uint32_t As = lds0 + st * G::AS * 16;
 #pragma unroll
     for (int j = 0; j < NAH; ++j) {
       const int q = j * 8 + w;
       const int g = q / (HW / 8) * (G::WTM / 8) + h * (HW / 8) + q % (HW / 8);
-      sa.load(kt, g, As + g * 64);
+      sa.load_at(kt, g, As + g * 1024);
     }
   };
 
@@ -625,6 +525,152 @@ __global__ __launch_bounds__(512) void gemm_alt_kernel(const bf16_t* __restrict_
   tile_epilogue<G, ROUNDS>(acc, smem, m0, bn, M, e, wm, wcol, tid);
 }
 
+// --------------------------------------------------------------------------- deep-ring kernel
+// Few rows: BM x BN tiles of one 32x32 block per multiplying wave, streamed through a
+// ring of S stages.  NW waves copy; the first (BM / 32) (BN / 32) of them multiply,
+// reading the fragments of k-step i + 1 under the MFMAs of k-step i.  K is summed in
+// order, as in the 8-wave tiles, so an element does not depend on the number of
+// rows or the tile.  The tile's columns are two runs of BN / 2 that the epilogue
+// pairs: gate and up, the two halves of a head, or (no pairs) neighbours.
+// Bound: the copies' latency (about 1.1 us) against the bytes in flight per CU, and
+// the serial MFMA chain of a k-step; so small tiles to fill the grid, rings of 72-144
+// KB, copies spread over waves that do not multiply, and no wait on the reads just
+// issued.  Against 128x128 tiles with 32 KB in flight: 16 rows, N = 4096, K = 14336 167 ->
+// 27 us, N = 6144, K = 4096 47 -> 11; 509 rows, N = 768, K = 3072 40 -> 9; 2048 rows, the
+// same weights, 43 -> 18; 300 rows, N = 4096, K = 14336 168 -> 67.  Splitting K between
+// wave groups gained at most 4 us at 16 rows and made sums depend on the tile.
+template <int BM, int BN, int NW, int S, class E>
+__global__ __launch_bounds__(64 * NW) void gemm_ring_kernel(const bf16_t* __restrict__ A, int64_t lda,
+                                                            const bf16_t* __restrict__ B, int64_t ldb, int M, int K,
+                                                            int d_ff, int n_bn, E e) {
+  constexpr int GW = (BM / 32) * (BN / 32), NT = 64 * NW, HB = BN / 2, CH = 8;
+  constexpr int SA = BM * CH, SS = (BM + BN) * CH;   // 16-byte slots of a stage's A tile, of a stage
+  constexpr int NG = (BM + BN) / 8, NL = NG / NW;    // 8-row groups of a stage, copies per wave
+  static_assert(NW >= GW && NG % NW == 0 && S >= 3 && (S - 2) * NL < 64, "copies split evenly");
+  constexpr int SP = BN + 4;                         // staged row in floats
+  static_assert(S * SS * 16 <= 160 * 1024 && BM * SP * 4 <= S * SS * 16, "LDS");
+  __shared__ __attribute__((aligned(16))) v4u smem[S * SS];
+  const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = w / (BN / 32), wn = w % (BN / 32);
+  int bm_, bn;
+  const int n_bm = (M + BM - 1) / BM;
+  xcd_tile((int)blockIdx.x, n_bm, n_bn, n_bm, &bm_, &bn);   // the row tiles of one column block together
+  const int m0 = bm_ * BM;
+  const ColRuns cr = e.template runs<HB>(bn, d_ff);
+  // this wave's 8-row groups: from A, or from either run of B
+  RowGroupSrc src[NL];
+#pragma unroll
+  for (int j = 0; j < NL; ++j) {
+    const int g = j * NW + w, rb = (g - BM / 8) * 8;
+    const bool isa = g < BM / 8;
+    const bf16_t* p = isa ? A + (int64_t)(m0 + g * 8) * lda
+                          : B + (int64_t)(rb < HB ? cr.b0 + rb : cr.b1 + rb - HB) * ldb;
+    src[j].init(p, isa ? lda : ldb, g, lane);
+  }
+  const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) v4u*)smem + w * 1024;
+  const int nk = K / kBK;
+  auto issue = [&](int kt, int slot) {
+#pragma unroll
+    for (int j = 0; j < NL; ++j) src[j].load_at(kt, 0, lds0 + slot * (SS * 16) + j * (NW * 1024));
+  };
+  f32x16_t acc;
+#pragma unroll
+  for (int i = 0; i < 16; ++i) acc[i] = 0.f;
+  bf16x8_t af[2][4], bf[2][4];
+#pragma unroll
+  for (int p = 0; p < S - 1; ++p)
+    if (p < nk) issue(p, p);
+  wait_steps_ahead<NL, S - 2>(min(nk, S - 1) - 1);
+  phase_barrier();
+  // Step i: stage i + 1 is in LDS for every wave and k-step i in registers; the slot
+  // of i - 1 is free (its fragments were multiplied before the barrier).  The
+  // copying steps and the last S - 1 run as separate loops.
+  auto run = [&](auto MUL) {
+    constexpr bool mul = decltype(MUL)::value;
+    int nxt = S - 1, rd = 0, i = 0;
+    auto read = [&](int h) {
+      const v4u* At = smem + rd * SS;
+      const v4u* Bt = At + SA;
+#pragma unroll
+      for (int ks = 0; ks < 4; ++ks) {
+        bf[h][ks] = frag<CH>(Bt, wn * 32 + l32, ks, lane);
+        af[h][ks] = frag<CH>(At, wm * 32 + l32, ks, lane);
+      }
+      rd = rd == S - 1 ? 0 : rd + 1;
+      __builtin_amdgcn_sched_barrier(0);
+    };
+    auto mma = [&](int h) {
+#pragma unroll
+      for (int ks = 0; ks < 4; ++ks) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bf[h][ks], af[h][ks], acc, 0, 0, 0);
+    };
+    auto step = [&](int h) {
+      wait_vmem_le<(S - 3) * NL>();
+      phase_barrier();
+      if constexpr (mul) read(h ^ 1);
+      issue(i + S - 1, nxt);
+      if constexpr (mul) mma(h);
+      nxt = nxt == S - 1 ? 0 : nxt + 1;
+      ++i;
+    };
+    auto last = [&](int h) {   // no more stages to copy
+      wait_steps_ahead<NL, S - 3>(nk - 2 - i);
+      phase_barrier();
+      if constexpr (mul) {
+        read(h ^ 1);
+        mma(h);
+      }
+      ++i;
+    };
+    if constexpr (mul) read(0);
+    while (i + S < nk) {
+      step(0);
+      step(1);
+    }
+    int h = 0;   // parity of i (even here)
+    if (i + S - 1 < nk) {
+      step(0);
+      h = 1;
+    }
+    if (h) {
+      while (i < nk - 2) {
+        last(1);
+        last(0);
+      }
+    } else {
+      while (i < nk - 2) {
+        last(0);
+        last(1);
+      }
+    }
+    if (i < nk - 1) {
+      if (h) last(1); else last(0);
+      h ^= 1;
+    }
+    if constexpr (mul) {
+      if (h) mma(1); else mma(0);
+    }
+  };
+  if (NW == GW || w < GW) run(std::true_type{});
+  else run(std::false_type{});
+  __syncthreads();   // the staging area overlaps the ring
+  float* Cs = reinterpret_cast<float*>(smem);
+  if (NW == GW || w < GW) {
+    // acc is the transposed block: lane l holds row l % 32, columns 8 g + 4 (l / 32) .. + 3
+    float* cs = Cs + (wm * 32 + l32) * SP + wn * 32 + (lane >> 5) * 4;
+#pragma unroll
+    for (int g = 0; g < 4; ++g) store4(cs + g * 8, make_float4(acc[4 * g], acc[4 * g + 1], acc[4 * g + 2], acc[4 * g + 3]));
+  }
+  __syncthreads();
+  constexpr int QPR = HB / 4;   // four-column units per run
+  for (int u = tid; u < BM * QPR; u += NT) {
+    const int r = u / QPR, c = u % QPR * 4, row = m0 + r;
+    if (row >= M) break;   // u grows with r
+    const float* cs = Cs + r * SP + c;
+    e.put(row, cr, c, *reinterpret_cast<const float4*>(cs), *reinterpret_cast<const float4*>(cs + HB));
+  }
+}
+
 // --------------------------------------------------------------------------- fp32 VALU kernel
 template <class E, bool SWIGLU>
 __global__ __launch_bounds__(256) void gemm_f32_kernel(const float* __restrict__ A, int64_t lda,
@@ -704,22 +750,56 @@ static int cu_count() {
   return n;
 }
 
-enum class Tile { k256x256, k256x192, k128x128 };
+// The tile with the least estimated time.  A launch takes
+//   rounds x (fixed + k-steps x step)   microseconds,
+// rounds = tiles / (CUs x workgroups per CU) rounded up; the constants are fits
+// (within about 15%) to times measured over M = 16 .. 65536 at the widths 256, 768, 4096.
+// The 8-wave tiles: 256x256 fixed 11.5, step 0.89 with a few tiles, up to 1.25 with every
+// CU busy; 256x192 11 and 0.78; 256x128 7.5 and 0.61 (1000 rows, N = 6144, K = 4096: 73, -,
+// 55 us; 2048 rows: 91, -, 114).  The ring tiles: 64x128 4.4 and 0.285; two workgroups
+// per CU: 64x64 3 and 0.195, 0.36 for two together, 32x64 3 and 0.13, 0.17, 32x32 3 and
+// 0.108, 0.13 (16 rows, N = 4096, K = 14336: 66, 45, 33, 27 us; 509 rows, N = 768, K = 3072:
+// 16, 11.9, 9.1, 10.6).  No tile beats the time the weights take from memory (5.5 TB/s);
+// among equals the one listed first is taken.
+enum class Tile { k32x64, k32x32, k64x64, k64x128, k256x128, k256x192, k256x256 };
 
 static Tile pick_tile(const GemmArgs& a, bool swiglu) {
-  const int ncu = cu_count();
-  const int64_t nm = (a.M + 255) / 256;
-  const bool fits256 = swiglu ? (a.d_ff % 128 == 0) : (a.N % 256 == 0);
-  // 192-wide tiles have three column blocks per wave, so their rotary pairs would
-  // go through the staged tile: measured slower than 256-wide tiles for q|k|v
-  const bool fits192 = !swiglu && a.N % 192 == 0 && a.epi != Epi::kStoreRope;
-  const int64_t tiles256 = fits256 ? nm * (a.N / 256) : 0, tiles192 = fits192 ? nm * (a.N / 192) : 0;
-  // fewer than half a wave of large tiles on the CUs (small M, e.g. window rows): 128x128 tiles
-  if (std::max(tiles256, tiles192) < ncu / 2) return Tile::k128x128;
-  // the 256-row tile whose last round of workgroups wastes least: cost = rounds x tile area
-  const int64_t c256 = fits256 ? (tiles256 + ncu - 1) / ncu * 256 : INT64_MAX;
-  const int64_t c192 = fits192 ? (tiles192 + ncu - 1) / ncu * 192 : INT64_MAX;
-  return c192 < c256 ? Tile::k256x192 : Tile::k256x256;
+  const int64_t ncu = cu_count(), nk = a.K / kBK;
+  const double mem = (double)a.N * a.K * 2 / 5.5e6;   // microseconds
+  double best = 1e30;
+  Tile tile = Tile::k32x64;
+  auto offer = [&](Tile t, double us) {
+    if (us < mem) us = mem;
+    if (us < best) { best = us; tile = t; }
+  };
+  auto tiles = [&](int bm, int bn) { return ((a.M + bm - 1) / bm) * (int64_t)(a.N / bn); };
+  auto rounds = [&](int64_t n, int64_t per) { return (double)((n + per - 1) / per); };
+  auto two = [&](Tile t, int bm, int bn, double alone, double both) {   // two workgroups per CU
+    const int64_t n = tiles(bm, bn);
+    offer(t, rounds(n, 2 * ncu) * (3.0 + nk * (n <= ncu ? alone : both)));
+  };
+  auto one = [&](Tile t, int bm, int bn, double fixed, double step, double load) {
+    const int64_t n = tiles(bm, bn);
+    offer(t, rounds(n, ncu) * (fixed + nk * step * (1.0 + load * (n < ncu ? (double)n / ncu : 1.0))));
+  };
+  two(Tile::k32x64, 32, 64, 0.13, 0.17);
+  two(Tile::k32x32, 32, 32, 0.108, 0.13);
+  two(Tile::k64x64, 64, 64, 0.195, 0.36);
+  // a 64-wide run does not fit a 64-wide head's half
+  if (a.epi != Epi::kStoreRope || a.head_dim == 128) one(Tile::k64x128, 64, 128, 4.4, 0.285, 0.0);
+  one(Tile::k256x128, 256, 128, 7.5, 0.61, 0.4);
+  // 192-wide tiles have three column blocks per wave: no pairs in registers
+  if (!swiglu && a.epi != Epi::kStoreRope && a.N % 192 == 0) one(Tile::k256x192, 256, 192, 11.0, 0.78, 0.4);
+  if (swiglu ? a.d_ff % 128 == 0 : a.N % 256 == 0) one(Tile::k256x256, 256, 256, 11.5, 0.89, 0.4);
+  return tile;
+}
+
+template <int BM, int BN, int NW, int S, class E>
+static hipError_t go_ring(const GemmArgs& a, const E& e, hipStream_t s) {
+  const int nbn = a.N / BN;
+  gemm_ring_kernel<BM, BN, NW, S, E><<<(a.M + BM - 1) / BM * nbn, 64 * NW, 0, s>>>(
+      (const bf16_t*)a.A, a.lda, (const bf16_t*)a.B, a.ldb, a.M, a.K, a.d_ff, nbn, e);
+  return hipGetLastError();
 }
 
 template <int BM, int BN, int NWM, int NWN, int PD, class E, bool SWIGLU>
@@ -730,13 +810,8 @@ static void go_pd(const GemmArgs& a, const E& e, hipStream_t s) {
   // (1-2% faster than 8 on q|k|v, output and down at 32768 rows, equal on
   // gate|up), 8 for short K
   const int group_m = a.K >= 4096 ? 4 : 8;
-  const bf16_t *A = (const bf16_t*)a.A, *B = (const bf16_t*)a.B;
-  if constexpr (NWM * NWN == 8)
-    gemm_alt_kernel<BM, BN, NWM, NWN, PD, E, SWIGLU>
-        <<<nbm * nbn, 512, 0, s>>>(A, a.lda, B, a.ldb, a.M, a.K, a.d_ff, nbn, group_m, e);
-  else
-    gemm_bf16_kernel<BM, BN, NWM, NWN, PD, E, SWIGLU>
-        <<<nbm * nbn, 64 * NWM * NWN, 0, s>>>(A, a.lda, B, a.ldb, a.M, a.K, a.d_ff, nbn, group_m, e);
+  gemm_alt_kernel<BM, BN, NWM, NWN, PD, E, SWIGLU><<<nbm * nbn, 512, 0, s>>>(
+      (const bf16_t*)a.A, a.lda, (const bf16_t*)a.B, a.ldb, a.M, a.K, a.d_ff, nbn, group_m, e);
 }
 
 // the pair distance each epilogue needs (plain layout when it pairs nothing)
@@ -759,10 +834,15 @@ static hipError_t go_bf16(const GemmArgs& a, const E& e, hipStream_t s) {
 template <class E, bool SWIGLU>
 static hipError_t go(const GemmArgs& a, bool bf16, const E& e, hipStream_t s) {
   if (bf16) {
+    if (E::kPaired && !SWIGLU && a.head_dim != 64 && a.head_dim != 128) return hipErrorInvalidValue;
     switch (pick_tile(a, SWIGLU)) {
-      case Tile::k256x256: return go_bf16<256, 256, E, SWIGLU, 2, 4>(a, e, s);
+      case Tile::k32x64: return go_ring<32, 64, 4, 6>(a, e, s);
+      case Tile::k32x32: return go_ring<32, 32, 4, 9>(a, e, s);
+      case Tile::k64x64: return go_ring<64, 64, 4, 5>(a, e, s);
+      case Tile::k64x128: return go_ring<64, 128, 8, 6>(a, e, s);
+      case Tile::k256x128: return go_bf16<256, 128, E, SWIGLU, 4, 2>(a, e, s);
       case Tile::k256x192: return go_bf16<256, 192, E, SWIGLU, 4, 2>(a, e, s);
-      case Tile::k128x128: return go_bf16<128, 128, E, SWIGLU, 2, 2>(a, e, s);
+      case Tile::k256x256: return go_bf16<256, 256, E, SWIGLU, 2, 4>(a, e, s);
     }
     return hipErrorInvalidValue;
   } else {

@@ -158,18 +158,6 @@ __device__ __forceinline__ void dma16_rows(const void* base, uint32_t nrec, uint
                : "memory");
 }
 
-// Wait until at most `ahead` k-steps of NL copies each (those issued after the
-// one about to be consumed) are still in flight; ahead <= K.
-template <int NL, int K>
-__device__ __forceinline__ void wait_steps_ahead(int ahead) {
-  if constexpr (K <= 0) {
-    wait_vmem();
-  } else {
-    if (ahead >= K) wait_vmem_le<NL * K>();
-    else wait_steps_ahead<NL, K - 1>(ahead);
-  }
-}
-
 template <int GMAX, int BK, int ST>
 __global__ __launch_bounds__(512) void lm_kl_kernel(const bf16_t* __restrict__ Xc, const bf16_t* __restrict__ Xp,
                                                     int64_t pass_stride, int G, const bf16_t* __restrict__ W,

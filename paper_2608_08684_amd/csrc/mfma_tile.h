@@ -109,16 +109,27 @@ struct RowGroupSrc {
     voff = (uint32_t)(lane / 8 * ld * 2 + ((lane % 8) ^ swz<8>(r)) * 16);
     group_bytes = __builtin_amdgcn_readfirstlane((int32_t)(8 * ld * 2));
   }
-  // group g (parity of w) of k-step kt to the 64 slots at dst
-  __device__ __forceinline__ void load(int kt, int g, v4u* dst) const {
-    const uint32_t lds = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(__attribute__((address_space(3))) v4u*)dst);
+  // group g (parity of w) of k-step kt to the 1024 bytes of LDS at `lds`
+  __device__ __forceinline__ void load_at(int kt, int g, uint32_t lds) const {
     const int32_t soff = __builtin_amdgcn_readfirstlane(kt * (kBK * 2) + g * group_bytes);
     asm volatile("s_nop 0\n\tbuffer_load_dwordx4 %0, %1, %2 offen lds"
                  :
-                 : "v"(voff), "s"(rsrc), "s"(soff), "{m0}"(lds)
+                 : "v"(voff), "s"(rsrc), "s"(soff), "{m0}"(__builtin_amdgcn_readfirstlane(lds))
                  : "memory");
   }
 };
+
+// Wait until at most `ahead` k-steps of NL copies each (those issued after the
+// one about to be consumed) are still in flight; ahead <= K.
+template <int NL, int K>
+__device__ __forceinline__ void wait_steps_ahead(int ahead) {
+  if constexpr (K <= 0) {
+    wait_vmem();
+  } else {
+    if (ahead >= K) wait_vmem_le<NL * K>();
+    else wait_steps_ahead<NL, K - 1>(ahead);
+  }
+}
 
 // Workgroup barrier without a wait of its own; nothing is moved across it.
 __device__ __forceinline__ void phase_barrier() {
