@@ -28,8 +28,7 @@
 //   * masks only on diagonal / ragged tiles;
 //   * the K fragment reads of a tile are issued up to six ahead of the MFMAs
 //     that consume them (scheduling groups), not each right before its use.
-// fp32 kernel: one thread per (row, head), streaming keys; for the small fp32
-// model only.
+// fp32 kernel: 32 queries of a head per workgroup on fp32 MFMAs.
 #include <math.h>
 
 #include <algorithm>
@@ -42,6 +41,7 @@ typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x4_t __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
 typedef float f32x16_t __attribute__((ext_vector_type(16)));
+typedef float f32x4_t __attribute__((ext_vector_type(4)));
 typedef short s16x4_t __attribute__((ext_vector_type(4)));
 typedef uint32_t v2u __attribute__((ext_vector_type(2)));
 typedef __attribute__((address_space(3))) void lds_void;
@@ -371,63 +371,164 @@ __global__ __launch_bounds__(64 * AttnTraits<DH>::kWaves, AttnTraits<DH>::kMinBl
   }
 }
 
+// fp32: one workgroup = 4 waves for 32 queries of one head.  The waves share out the
+// 32-key blocks (wave w takes blocks w, w + 4, ...), each with its own running
+// maximum, denominator and output, merged through LDS in wave order.  S^T = K Q^T and
+// O^T = V^T P^T on v_mfma_f32_32x32x2_f32, softmax with expf.  In S^T a half-wave
+// holds the dimensions hf d_h / 2 .. of its row, so K and Q rows are read as 16-byte
+// pieces; lane l then owns query l % 32 and the keys 8 (i / 4) + 4 hf + i % 4, and the key
+// order of O^T is that of those registers.
+// Bound: latency of a block's two MFMA chains (2 x d_h x 32 cycles) and of its loads.
+// Against one thread per (row, head) walking the keys: 256 rows, 4 heads of 64 276 us,
+// 1024 + 777 rows, 12 heads of 64 1216 us.
 template <int DH>
-__global__ __launch_bounds__(64) void attn_f32_kernel(const float* __restrict__ qkv, int64_t ldq,
-                                                      float* __restrict__ out, int64_t ldo, SeqTable st, int H,
-                                                      int Hkv, float scale) {
-  const int r = blockIdx.x * 64 + threadIdx.x;
-  if (r >= st.rows) return;
-  const int hq = blockIdx.y, hk = hq / (H / Hkv);
-  const int k = seq_of_row(st, r), row0 = st.off[k], q = r - row0;
-  float qv[DH], acc[DH];
-  const float* qp = qkv + (int64_t)r * ldq + (int64_t)hq * DH;
-#pragma unroll
-  for (int j = 0; j < DH; ++j) { qv[j] = qp[j]; acc[j] = 0.f; }
-  float m = -INFINITY, l = 0.f;
-  for (int u = 0; u <= q; ++u) {
-    const float* kp = qkv + (int64_t)(row0 + u) * ldq + (int64_t)H * DH + (int64_t)hk * DH;
-    const float* vp = qkv + (int64_t)(row0 + u) * ldq + (int64_t)(H + Hkv) * DH + (int64_t)hk * DH;
-    float sdot = 0.f;
-#pragma unroll
-    for (int j = 0; j < DH; ++j) sdot = fmaf(qv[j], kp[j], sdot);
-    sdot *= scale;
-    const float m_new = fmaxf(m, sdot);
-    const float corr = expf(m - m_new), p = expf(sdot - m_new);
-    l = l * corr + p;
-#pragma unroll
-    for (int j = 0; j < DH; ++j) acc[j] = fmaf(p, vp[j], acc[j] * corr);
-    m = m_new;
+__global__ __launch_bounds__(256) void attn_f32_kernel(const float* __restrict__ qkv, int64_t ldq,
+                                                       float* __restrict__ out, int64_t ldo, SeqTable st, AttnWork wk,
+                                                       int H, int Hkv, float scale) {
+  constexpr int HD = DH / 2, NDB = DH / 32, SP = DH + 4;
+  __shared__ __attribute__((aligned(16))) float so[4][32 * SP];
+  __shared__ float sm[4][32], sl[4][32];
+  const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, hf = lane >> 5;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int item = blockIdx.x / H, hq = blockIdx.x - item * H, hk = hq / (H / Hkv);
+  int lo = 0, hi = st.n - 1;
+  while (lo < hi) {
+    const int mid = (lo + hi + 1) >> 1;
+    if (wk.cum[mid] <= item) lo = mid; else hi = mid - 1;
   }
-  float* op = out + (int64_t)r * ldo + (int64_t)hq * DH;
-  const float inv = 1.0f / l;
+  const int k = wk.order[lo], row0 = st.off[k], T = st.off[k + 1] - row0;
+  const int qb = (T + 31) / 32 - 1 - (item - wk.cum[lo]), q0 = qb * 32;   // longest first
+  const int my_q = min(q0 + l32, T - 1);   // rows past T duplicate row T - 1
+  const float* kbase = qkv + (int64_t)row0 * ldq + (int64_t)(H + hk) * DH;
+  const float* vbase = kbase + (int64_t)Hkv * DH;
+  f32x4_t qf[HD / 4];
+  {
+    const float* qp = qkv + (int64_t)(row0 + my_q) * ldq + (int64_t)hq * DH + hf * HD;
 #pragma unroll
-  for (int j = 0; j < DH; ++j) op[j] = acc[j] * inv;
+    for (int j = 0; j < HD / 4; ++j) qf[j] = *reinterpret_cast<const f32x4_t*>(qp + 4 * j);
+  }
+  f32x16_t o[NDB];
+#pragma unroll
+  for (int db = 0; db < NDB; ++db)
+#pragma unroll
+    for (int i = 0; i < 16; ++i) o[db][i] = 0.f;
+  float m = -INFINITY, l = 0.f;
+  for (int kb = w; kb <= qb; kb += 4) {
+    const int k0 = kb * 32;
+    f32x16_t s;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) s[i] = 0.f;
+    const float* kp = kbase + (int64_t)min(k0 + l32, T - 1) * ldq + hf * HD;
+#pragma unroll
+    for (int j = 0; j < HD / 4; ++j) {
+      const f32x4_t kf = *reinterpret_cast<const f32x4_t*>(kp + 4 * j);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) s = __builtin_amdgcn_mfma_f32_32x32x2f32(kf[e], qf[j][e], s, 0, 0, 0);
+    }
+    float mx = -INFINITY;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      const int key = k0 + (i >> 2) * 8 + hf * 4 + (i & 3);
+      s[i] = key <= my_q ? s[i] * scale : -INFINITY;
+      mx = fmaxf(mx, s[i]);
+    }
+    mx = max_halves(mx);
+    const float m_new = fmaxf(m, mx);   // block 0 holds a key of every query; later blocks follow a finite m or start one
+    const float ref = m_new == -INFINITY ? 0.f : m_new;
+    const float corr = m == -INFINITY ? 0.f : expf(m - ref);
+    float sum = 0.f;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      s[i] = expf(s[i] - ref);
+      sum += s[i];
+    }
+    l = l * corr + sum;
+    m = m_new;
+#pragma unroll
+    for (int db = 0; db < NDB; ++db)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) o[db][i] *= corr;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      const float* vp = vbase + (int64_t)min(k0 + (i >> 2) * 8 + hf * 4 + (i & 3), T - 1) * ldq + l32;
+#pragma unroll
+      for (int db = 0; db < NDB; ++db) o[db] = __builtin_amdgcn_mfma_f32_32x32x2f32(vp[db * 32], s[i], o[db], 0, 0, 0);
+    }
+  }
+  l = sum_halves(l);
+  if (hf == 0) {
+    sm[w][l32] = m;
+    sl[w][l32] = l;
+  }
+#pragma unroll
+  for (int db = 0; db < NDB; ++db)
+#pragma unroll
+    for (int g = 0; g < 4; ++g)
+      *reinterpret_cast<f32x4_t*>(&so[w][l32 * SP + db * 32 + g * 8 + hf * 4]) =
+          f32x4_t{o[db][4 * g], o[db][4 * g + 1], o[db][4 * g + 2], o[db][4 * g + 3]};
+  __syncthreads();
+  const int q = tid >> 3, row = q0 + q;
+  if (row >= T) return;
+  float M = sm[0][q];   // wave 0 holds block 0: finite
+#pragma unroll
+  for (int j = 1; j < 4; ++j) M = fmaxf(M, sm[j][q]);
+  float f[4], L = 0.f;
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    f[j] = sm[j][q] == -INFINITY ? 0.f : expf(sm[j][q] - M);
+    L += sl[j][q] * f[j];
+  }
+  const float inv = 1.0f / L;
+  float* op = out + (int64_t)(row0 + row) * ldo + (int64_t)hq * DH;
+#pragma unroll
+  for (int c = (tid & 7) * 4; c < DH; c += 32) {
+    f32x4_t a = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const f32x4_t x = *reinterpret_cast<const f32x4_t*>(&so[j][q * SP + c]);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) a[e] += x[e] * f[j];
+    }
+#pragma unroll
+    for (int e = 0; e < 4; ++e) a[e] *= inv;
+    *reinterpret_cast<f32x4_t*>(op + c) = a;
+  }
+}
+
+// Work items of a launch: sequences by decreasing length; items[k] per sequence.
+template <class F>
+static AttnWork attn_work(const SeqTable& st, const F& items) {
+  AttnWork wk;
+  for (int k = 0; k < st.n; ++k) wk.order[k] = k;
+  for (int a = 1; a < st.n; ++a) {  // insertion sort, stable
+    const int v = wk.order[a], len = st.off[v + 1] - st.off[v];
+    int b = a;
+    while (b > 0 && st.off[wk.order[b - 1] + 1] - st.off[wk.order[b - 1]] < len) {
+      wk.order[b] = wk.order[b - 1];
+      --b;
+    }
+    wk.order[b] = v;
+  }
+  wk.cum[0] = 0;
+  for (int j = 0; j < st.n; ++j) {
+    const int k = wk.order[j];
+    wk.cum[j + 1] = wk.cum[j] + items(st.off[k + 1] - st.off[k]);
+  }
+  wk.total = wk.cum[st.n];
+  return wk;
 }
 
 hipError_t launch_attention(const void* qkv, int64_t ldq, void* out, int64_t ldo, const SeqTable& st, int n_heads,
                             int n_kv_heads, int head_dim, bool bf16, hipStream_t s, const KvPrefix* prefix) {
   if (st.rows <= 0) return hipSuccess;
   if (bf16) {
-    // sequences by decreasing length; items = pairs of q-blocks
-    AttnWork wk;
-    for (int k = 0; k < st.n; ++k) wk.order[k] = k;
-    for (int a = 1; a < st.n; ++a) {  // insertion sort, stable
-      const int v = wk.order[a], len = st.off[v + 1] - st.off[v];
-      int b = a;
-      while (b > 0 && st.off[wk.order[b - 1] + 1] - st.off[wk.order[b - 1]] < len) {
-        wk.order[b] = wk.order[b - 1];
-        --b;
-      }
-      wk.order[b] = v;
-    }
     const bool pre = prefix && prefix->P > 0;
     const int bq = 32 * (head_dim == 64 ? AttnTraits<64>::kWaves : AttnTraits<128>::kWaves);   // queries per block
-    wk.cum[0] = 0;
-    for (int j = 0; j < st.n; ++j) {
-      const int k = wk.order[j], nqb = (st.off[k + 1] - st.off[k] + bq - 1) / bq;
-      wk.cum[j + 1] = wk.cum[j] + (pre ? nqb : (nqb + 1) / 2);
-    }
-    wk.total = wk.cum[st.n];
+    // items = pairs of q-blocks, or single q-blocks behind a cached prefix
+    const AttnWork wk = attn_work(st, [&](int len) {
+      const int nqb = (len + bq - 1) / bq;
+      return pre ? nqb : (nqb + 1) / 2;
+    });
     if (wk.total == 0) return hipSuccess;
     // the buffer descriptor covers one sequence's rows with 32-bit byte offsets
     if ((int64_t)st.max_len * ldq * 2 >= ((int64_t)1 << 31) || n_heads % n_kv_heads != 0) return hipErrorInvalidValue;
@@ -452,15 +553,17 @@ hipError_t launch_attention(const void* qkv, int64_t ldq, void* out, int64_t ldo
   } else {
     if (prefix && prefix->P > 0) return hipErrorInvalidValue;   // cached prefixes: bf16 path only
     const float scale = (float)(1.0 / sqrt((double)head_dim));
-    dim3 grid((st.rows + 63) / 64, n_heads);
-    if (head_dim == 32)
-      attn_f32_kernel<32><<<grid, 64, 0, s>>>((const float*)qkv, ldq, (float*)out, ldo, st, n_heads, n_kv_heads, scale);
-    else if (head_dim == 64)
-      attn_f32_kernel<64><<<grid, 64, 0, s>>>((const float*)qkv, ldq, (float*)out, ldo, st, n_heads, n_kv_heads, scale);
-    else if (head_dim == 128)
-      attn_f32_kernel<128><<<grid, 64, 0, s>>>((const float*)qkv, ldq, (float*)out, ldo, st, n_heads, n_kv_heads, scale);
-    else
-      return hipErrorInvalidValue;
+    const AttnWork wk = attn_work(st, [](int len) { return (len + 31) / 32; });
+    if (n_heads % n_kv_heads != 0 || (int64_t)wk.total * n_heads > INT32_MAX) return hipErrorInvalidValue;
+    const int grid = wk.total * n_heads;
+#define RK_ATTN32(D)                                                                                        \
+  attn_f32_kernel<D><<<grid, 256, 0, s>>>((const float*)qkv, ldq, (float*)out, ldo, st, wk, n_heads, n_kv_heads, \
+                                          scale)
+    if (head_dim == 32) RK_ATTN32(32);
+    else if (head_dim == 64) RK_ATTN32(64);
+    else if (head_dim == 128) RK_ATTN32(128);
+    else return hipErrorInvalidValue;
+#undef RK_ATTN32
   }
   return hipGetLastError();
 }
