@@ -9,8 +9,7 @@
 // K-steps streamed global -> LDS by buffer loads into rings of LDS stages (see
 // mfma_tile.h).  The finished tile leaves through LDS so the global accesses are
 // whole rows; a rotary pair j, j + d_h/2 or a gate/up pair always lies inside one tile.
-// fp32 path: a VALU kernel with the same epilogues (64x128 tile), staged 64 rows
-// at a time.
+// fp32 path: the deep-ring tiles on v_mfma_f32_32x32x2_f32.
 #include "mfma_tile.h"
 
 #include <algorithm>
@@ -19,20 +18,10 @@
 
 namespace rk {
 
-constexpr int kCsStride = 132;  // staged tile row stride in floats (128 + pad)
-
 // --------------------------------------------------------------------------- stores of 8 values
 __device__ __forceinline__ void store8(float* p, const float* v) {
   reinterpret_cast<float4*>(p)[0] = make_float4(v[0], v[1], v[2], v[3]);
   reinterpret_cast<float4*>(p)[1] = make_float4(v[4], v[5], v[6], v[7]);
-}
-__device__ __forceinline__ void store8(bf16_t* p, const float* v) {
-  v4u u;
-  u.x = (uint32_t)f2bf(v[0]) | ((uint32_t)f2bf(v[1]) << 16);
-  u.y = (uint32_t)f2bf(v[2]) | ((uint32_t)f2bf(v[3]) << 16);
-  u.z = (uint32_t)f2bf(v[4]) | ((uint32_t)f2bf(v[5]) << 16);
-  u.w = (uint32_t)f2bf(v[6]) | ((uint32_t)f2bf(v[7]) << 16);
-  *reinterpret_cast<v4u*>(p) = u;
 }
 
 // 4 values to 4 consecutive elements (16 bytes fp32, 8 bytes bf16)
@@ -67,33 +56,6 @@ struct EpiRope {
   static constexpr int pair_dist(int, int head_dim) { return head_dim / 2; }
   // tab[pos * head_dim/2 + j] = (cos, sin) of position pos, pair j; pos[row] = position of the row
   O* out; int64_t ldo; int rope_cols; int head_dim; const float2* tab; const int32_t* pos; int q_cols; float q_scale;
-  template <int BN>
-  __device__ void apply(int row, int bn, int c0, const float* cs) const {
-    const int gc0 = bn * BN + c0;
-    O* dst = out + (int64_t)row * ldo + gc0;
-    if (gc0 >= rope_cols) {  // value columns: no rotation
-      store8(dst, cs + c0);
-      return;
-    }
-    // the 8 columns lie in one half of one head: pairs jh0..jh0+7 with partners at +-half
-    const int half = head_dim >> 1;
-    const int jh = gc0 & (head_dim - 1);
-    const bool lo = jh < half;
-    const int j0 = lo ? jh : jh - half;
-    const float4* t4 = reinterpret_cast<const float4*>(tab + (int64_t)pos[row] * half + j0);
-    const float* x = cs + c0;
-    const float* y = cs + c0 + (lo ? half : -half);
-    const float sg = lo ? -1.0f : 1.0f;
-    const float sc = gc0 < q_cols ? q_scale : 1.0f;
-    float v[8];
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const float4 t = t4[q];  // (cos, sin) of pairs 2q and 2q+1
-      v[2 * q] = fmaf(sg * y[2 * q], t.y, x[2 * q] * t.x) * sc;
-      v[2 * q + 1] = fmaf(sg * y[2 * q + 1], t.w, x[2 * q + 1] * t.z) * sc;
-    }
-    store8(dst, v);
-  }
   // register form: x = tile columns tc..tc+3 (first half of a head), y = their
   // partners head_dim/2 further on; o0, o1 = the outputs at the same columns
   using stage_t = O;
@@ -160,6 +122,8 @@ struct EpiSwiGLU {
   static constexpr bool kPaired = true;
   static constexpr int pair_dist(int BN, int) { return BN / 2; }
   O* out; int64_t ldo;
+  // silu(g) u, silu(g) = g / (1 + e^-g) with the hardware exp2 and reciprocal (about 1
+  // ulp each)
   static __device__ __forceinline__ float silu_mul(float g, float u) {
     return g * __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(-g * 1.4426950408889634f)) * u;
   }
@@ -178,19 +142,6 @@ struct EpiSwiGLU {
   __device__ __forceinline__ void put(int row, const ColRuns& cr, int c, float4 x, float4 y) const {
     store4(out + (int64_t)row * ldo + cr.o0 + c, make_float4(silu_mul(x.x, y.x), silu_mul(x.y, y.y),
                                                              silu_mul(x.z, y.z), silu_mul(x.w, y.w)));
-  }
-  template <int BN>
-  __device__ void apply(int row, int bn, int c0, const float* cs) const {
-    // silu(g) = g / (1 + e^-g) with the hardware exp2 and reciprocal (about 1 ulp
-    // each); the product is rounded to bf16 (or stored fp32 on the fp32 path).
-    float v[8];
-#pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      const float g = cs[c0 + j], u = cs[BN / 2 + c0 + j];
-      const float sig = __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(-g * 1.4426950408889634f));
-      v[j] = g * sig * u;
-    }
-    store8(out + (int64_t)row * ldo + (int64_t)bn * (BN / 2) + c0, v);
   }
 };
 
@@ -212,26 +163,6 @@ struct EpiStoreF32 {
     store8(out + (int64_t)row * ldo + (int64_t)bn * BN + c0, cs + c0);
   }
 };
-
-// Run the epilogue over 64 staged rows (row stride BN + 4 floats) with NT threads.
-template <int BN, class E, int NT = 256>
-__device__ __forceinline__ void run_epilogue(const E& e, const float* Cs, int row0, int M, int bn) {
-  constexpr int TPR = E::out_cols(BN) / 8;
-  constexpr int RPP = NT / TPR;
-  const int t = threadIdx.x;
-  const int c0 = (t % TPR) * 8;
-  for (int r = t / TPR; r < 64; r += RPP) {
-    const int row = row0 + r;
-    if (row < M) e.template apply<BN>(row, bn, c0, Cs + r * (BN + 4));
-  }
-}
-
-// Row of B feeding tile column n of column-block bn (fp32 path, 128-wide tiles).
-template <bool SWIGLU>
-__device__ __forceinline__ int b_row(int bn, int n, int d_ff) {
-  if (SWIGLU) return n < 64 ? bn * 64 + n : d_ff + bn * 64 + (n - 64);
-  return bn * 128 + n;
-}
 
 // --------------------------------------------------------------------------- bf16 MFMA kernels
 // Wave layout.  PD: distance in tile columns between the two values an epilogue
@@ -539,10 +470,17 @@ __global__ __launch_bounds__(512) void gemm_alt_kernel(const bf16_t* __restrict_
 // 27 us, N = 6144, K = 4096 47 -> 11; 509 rows, N = 768, K = 3072 40 -> 9; 2048 rows, the
 // same weights, 43 -> 18; 300 rows, N = 4096, K = 14336 168 -> 67.  Splitting K between
 // wave groups gained at most 4 us at 16 rows and made sums depend on the tile.
-template <int BM, int BN, int NW, int S, class E>
-__global__ __launch_bounds__(64 * NW) void gemm_ring_kernel(const bf16_t* __restrict__ A, int64_t lda,
-                                                            const bf16_t* __restrict__ B, int64_t ldb, int M, int K,
+// fp32 (T = float): the same with 128-byte k-steps of 32 values and
+// v_mfma_f32_32x32x2_f32; each k-step is summed from zero and then added, so the
+// rounding error grows with K / 32 + 32 terms, not K.  Bound: the matrix cores (a k-step
+// is 1024 cycles per block, 157 TFLOP/s over the chip).  Against the vector units
+// with a 64x128 tile: 1801 rows, N = 32000, K = 768 73 TFLOP/s, N = 768, K = 3072 28;
+// 256 rows, N = 256, K = 1024 97 us.
+template <typename T, int BM, int BN, int NW, int S, class E>
+__global__ __launch_bounds__(64 * NW) void gemm_ring_kernel(const T* __restrict__ A, int64_t lda,
+                                                            const T* __restrict__ B, int64_t ldb, int M, int K,
                                                             int d_ff, int n_bn, E e) {
+  constexpr bool F32 = sizeof(T) == 4;
   constexpr int GW = (BM / 32) * (BN / 32), NT = 64 * NW, HB = BN / 2, CH = 8;
   constexpr int SA = BM * CH, SS = (BM + BN) * CH;   // 16-byte slots of a stage's A tile, of a stage
   constexpr int NG = (BM + BN) / 8, NL = NG / NW;    // 8-row groups of a stage, copies per wave
@@ -564,12 +502,12 @@ __global__ __launch_bounds__(64 * NW) void gemm_ring_kernel(const bf16_t* __rest
   for (int j = 0; j < NL; ++j) {
     const int g = j * NW + w, rb = (g - BM / 8) * 8;
     const bool isa = g < BM / 8;
-    const bf16_t* p = isa ? A + (int64_t)(m0 + g * 8) * lda
-                          : B + (int64_t)(rb < HB ? cr.b0 + rb : cr.b1 + rb - HB) * ldb;
-    src[j].init(p, isa ? lda : ldb, g, lane);
+    const T* p = isa ? A + (int64_t)(m0 + g * 8) * lda
+                     : B + (int64_t)(rb < HB ? cr.b0 + rb : cr.b1 + rb - HB) * ldb;
+    src[j].init(reinterpret_cast<const bf16_t*>(p), (isa ? lda : ldb) * (sizeof(T) / 2), g, lane);
   }
   const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) v4u*)smem + w * 1024;
-  const int nk = K / kBK;
+  const int nk = K / (128 / (int)sizeof(T));
   auto issue = [&](int kt, int slot) {
 #pragma unroll
     for (int j = 0; j < NL; ++j) src[j].load_at(kt, 0, lds0 + slot * (SS * 16) + j * (NW * 1024));
@@ -601,8 +539,23 @@ __global__ __launch_bounds__(64 * NW) void gemm_ring_kernel(const bf16_t* __rest
       __builtin_amdgcn_sched_barrier(0);
     };
     auto mma = [&](int h) {
+      if constexpr (F32) {
+        f32x16_t part;
 #pragma unroll
-      for (int ks = 0; ks < 4; ++ks) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bf[h][ks], af[h][ks], acc, 0, 0, 0);
+        for (int q = 0; q < 16; ++q) part[q] = 0.f;
+#pragma unroll
+        for (int ks = 0; ks < 4; ++ks) {
+          const f32x4_t x = __builtin_bit_cast(f32x4_t, af[h][ks]), y = __builtin_bit_cast(f32x4_t, bf[h][ks]);
+#pragma unroll
+          for (int q = 0; q < 4; ++q) part = __builtin_amdgcn_mfma_f32_32x32x2f32(y[q], x[q], part, 0, 0, 0);
+        }
+#pragma unroll
+        for (int q = 0; q < 16; ++q) acc[q] += part[q];
+      } else {
+#pragma unroll
+        for (int ks = 0; ks < 4; ++ks)
+          acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bf[h][ks], af[h][ks], acc, 0, 0, 0);
+      }
     };
     auto step = [&](int h) {
       wait_vmem_le<(S - 3) * NL>();
@@ -671,72 +624,6 @@ __global__ __launch_bounds__(64 * NW) void gemm_ring_kernel(const bf16_t* __rest
   }
 }
 
-// --------------------------------------------------------------------------- fp32 VALU kernel
-template <class E, bool SWIGLU>
-__global__ __launch_bounds__(256) void gemm_f32_kernel(const float* __restrict__ A, int64_t lda,
-                                                       const float* __restrict__ B, int64_t ldb, int M, int K,
-                                                       int d_ff, E e) {
-  __shared__ __attribute__((aligned(16))) float smem[64 * kCsStride];
-  static_assert(kCsStride == 128 + 4, "fp32 path stages 128-wide tiles");
-  float* As = smem;             // [16][68]  k-major
-  float* Bs = smem + 16 * 68;   // [16][132] k-major
-  const int tid = threadIdx.x, ty = tid >> 4, tx = tid & 15;
-  const int bn = blockIdx.x, m0 = blockIdx.y * 64;
-  const int lrow = tid >> 2, kq = (tid & 3) * 4;
-  const float* pa = A + (int64_t)min(m0 + lrow, M - 1) * lda + kq;
-  const float* pb0 = B + (int64_t)b_row<SWIGLU>(bn, lrow, d_ff) * ldb + kq;
-  const float* pb1 = B + (int64_t)b_row<SWIGLU>(bn, lrow + 64, d_ff) * ldb + kq;
-  float acc[4][8];
-#pragma unroll
-  for (int i = 0; i < 4; ++i)
-#pragma unroll
-    for (int j = 0; j < 8; ++j) acc[i][j] = 0.f;
-  for (int k0 = 0; k0 < K; k0 += 16) {
-    const float4 a = *reinterpret_cast<const float4*>(pa + k0);
-    const float4 b0 = *reinterpret_cast<const float4*>(pb0 + k0);
-    const float4 b1 = *reinterpret_cast<const float4*>(pb1 + k0);
-    __syncthreads();
-    As[(kq + 0) * 68 + lrow] = a.x; As[(kq + 1) * 68 + lrow] = a.y;
-    As[(kq + 2) * 68 + lrow] = a.z; As[(kq + 3) * 68 + lrow] = a.w;
-    Bs[(kq + 0) * 132 + lrow] = b0.x; Bs[(kq + 1) * 132 + lrow] = b0.y;
-    Bs[(kq + 2) * 132 + lrow] = b0.z; Bs[(kq + 3) * 132 + lrow] = b0.w;
-    Bs[(kq + 0) * 132 + lrow + 64] = b1.x; Bs[(kq + 1) * 132 + lrow + 64] = b1.y;
-    Bs[(kq + 2) * 132 + lrow + 64] = b1.z; Bs[(kq + 3) * 132 + lrow + 64] = b1.w;
-    __syncthreads();
-    // blocked summation: each 16-wide k-chunk in a fresh partial, then added to
-    // the running sum, so the rounding error grows with K / 16 + 16 terms, not K
-    float part[4][8];
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-      for (int j = 0; j < 8; ++j) part[i][j] = 0.f;
-#pragma unroll
-    for (int k = 0; k < 16; ++k) {
-      float av[4], bv[8];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) av[i] = As[k * 68 + ty * 4 + i];
-#pragma unroll
-      for (int j = 0; j < 8; ++j) bv[j] = Bs[k * 132 + tx * 8 + j];
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 8; ++j) part[i][j] = fmaf(av[i], bv[j], part[i][j]);
-    }
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-      for (int j = 0; j < 8; ++j) acc[i][j] += part[i][j];
-  }
-  __syncthreads();
-  float* Cs = smem;
-#pragma unroll
-  for (int i = 0; i < 4; ++i)
-#pragma unroll
-    for (int j = 0; j < 8; ++j) Cs[(ty * 4 + i) * kCsStride + tx * 8 + j] = acc[i][j];
-  __syncthreads();
-  run_epilogue<128>(e, Cs, m0, M, bn);
-}
-
 // --------------------------------------------------------------------------- dispatch
 static int cu_count() {
   static int n = 0;
@@ -794,11 +681,11 @@ static Tile pick_tile(const GemmArgs& a, bool swiglu) {
   return tile;
 }
 
-template <int BM, int BN, int NW, int S, class E>
+template <typename T, int BM, int BN, int NW, int S, class E>
 static hipError_t go_ring(const GemmArgs& a, const E& e, hipStream_t s) {
   const int nbn = a.N / BN;
-  gemm_ring_kernel<BM, BN, NW, S, E><<<(a.M + BM - 1) / BM * nbn, 64 * NW, 0, s>>>(
-      (const bf16_t*)a.A, a.lda, (const bf16_t*)a.B, a.ldb, a.M, a.K, a.d_ff, nbn, e);
+  gemm_ring_kernel<T, BM, BN, NW, S, E><<<(a.M + BM - 1) / BM * nbn, 64 * NW, 0, s>>>(
+      (const T*)a.A, a.lda, (const T*)a.B, a.ldb, a.M, a.K, a.d_ff, nbn, e);
   return hipGetLastError();
 }
 
@@ -836,22 +723,25 @@ static hipError_t go(const GemmArgs& a, bool bf16, const E& e, hipStream_t s) {
   if (bf16) {
     if (E::kPaired && !SWIGLU && a.head_dim != 64 && a.head_dim != 128) return hipErrorInvalidValue;
     switch (pick_tile(a, SWIGLU)) {
-      case Tile::k32x64: return go_ring<32, 64, 4, 6>(a, e, s);
-      case Tile::k32x32: return go_ring<32, 32, 4, 9>(a, e, s);
-      case Tile::k64x64: return go_ring<64, 64, 4, 5>(a, e, s);
-      case Tile::k64x128: return go_ring<64, 128, 8, 6>(a, e, s);
+      case Tile::k32x64: return go_ring<bf16_t, 32, 64, 4, 6>(a, e, s);
+      case Tile::k32x32: return go_ring<bf16_t, 32, 32, 4, 9>(a, e, s);
+      case Tile::k64x64: return go_ring<bf16_t, 64, 64, 4, 5>(a, e, s);
+      case Tile::k64x128: return go_ring<bf16_t, 64, 128, 8, 6>(a, e, s);
       case Tile::k256x128: return go_bf16<256, 128, E, SWIGLU, 4, 2>(a, e, s);
       case Tile::k256x192: return go_bf16<256, 192, E, SWIGLU, 4, 2>(a, e, s);
       case Tile::k256x256: return go_bf16<256, 256, E, SWIGLU, 2, 4>(a, e, s);
     }
     return hipErrorInvalidValue;
   } else {
-    const int nbn = SWIGLU ? a.d_ff / 64 : a.N / 128;
-    dim3 grid(nbn, (a.M + 63) / 64);
-    gemm_f32_kernel<E, SWIGLU><<<grid, 256, 0, s>>>((const float*)a.A, a.lda, (const float*)a.B, a.ldb, a.M, a.K,
-                                                    a.d_ff, e);
+    // 64x64 tiles keep the four matrix cores of a CU busy; with fewer tiles than CUs,
+    // 32x32 tiles spread the work over four times as many (a block's serial chain is
+    // the same).  The two runs of a 32-wide head's halves are 16 columns.
+    const bool narrow = E::kPaired && !SWIGLU && a.head_dim < 64;
+    const int64_t n64 = (int64_t)((a.M + 63) / 64) * (a.N / 64);
+    if (n64 < cu_count()) return go_ring<float, 32, 32, 4, 9>(a, e, s);
+    if (narrow) return go_ring<float, 64, 32, 4, 6>(a, e, s);
+    return go_ring<float, 64, 64, 4, 5>(a, e, s);
   }
-  return hipGetLastError();
 }
 
 hipError_t launch_gemm(const GemmArgs& a, bool bf16, hipStream_t s) {

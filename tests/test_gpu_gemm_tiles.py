@@ -69,7 +69,8 @@ def check_block(m, lengths, tol=7.5e-3, big=0.06):
     import torch
     import paper_2608_08684_amd as rk
     g = torch.Generator(device="cuda").manual_seed(5)
-    mat = lambda r, c, s=None: torch.empty(r, c, device="cuda", dtype=torch.bfloat16).normal_(
+    dtype = torch.float32 if m.dtype == "f32" else torch.bfloat16
+    mat = lambda r, c, s=None: torch.empty(r, c, device="cuda", dtype=dtype).normal_(
         0, s or c ** -0.5, generator=g)
     gain = lambda: 1.0 + 0.2 * torch.randn(m.d_model, device="cuda", generator=g)
     qkv, att = (m.n_heads + 2 * m.n_kv_heads) * m.head_dim, m.n_heads * m.head_dim
@@ -151,3 +152,18 @@ def test_rows_do_not_depend_on_the_batch():
         got.append(h[1, -40:].clone())
     for x in got[1:]:
         assert torch.equal(x, got[0])
+
+
+# fp32: the same block on the fp32 tiles and the fp32 attention, head dims 32, 64 and 128, one row to several
+# 32-query blocks, many and few tiles.  fp32 sums of up to 1000 terms in chunks of 32: about sqrt(64) * 6e-8 = 5e-7
+# relative per product of the block, a few of them in a row
+@pytest.mark.parametrize("m, lengths", [
+    (Shape(128, 4, 2, 32, 64), [1, 31, 32, 33, 1]),
+    (Shape(256, 4, 4, 64, 192), [256, 129, 3]),
+    (Shape(384, 4, 1, 128, 320), [100, 161]),
+    (Shape(512, 16, 4, 32, 1024), [900, 1200, 77]),
+    (Shape(1024, 16, 16, 64, 704), [1500, 333]),
+], ids=["hd32", "hd64", "hd128", "hd32-many", "hd64-many"])
+def test_fp32_block(m, lengths):
+    m.dtype = "f32"
+    check_block(m, lengths, tol=2e-6, big=2e-5)
