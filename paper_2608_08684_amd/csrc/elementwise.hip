@@ -8,48 +8,68 @@
 namespace rk {
 
 // --------------------------------------------------------------------------- embedding
+// A token's row in groups of four values (d a multiple of 4): one 8-byte (bf16) or
+// 16-byte load and one 16-byte store (32768 rows of 4096: 291 us with single values).
+// V: the table is aligned to such a group; otherwise its values are read singly.
+__device__ __forceinline__ void load4v(const float* p, float& a, float& b, float& c, float& d);
+__device__ __forceinline__ void load4v(const bf16_t* p, float& a, float& b, float& c, float& d);
+
+template <typename E, bool V>
+__device__ __forceinline__ float4 emb4(const E* p) {
+  float4 v;
+  if constexpr (V) load4v(p, v.x, v.y, v.z, v.w);
+  else v = make_float4(Act<E>::load(p), Act<E>::load(p + 1), Act<E>::load(p + 2), Act<E>::load(p + 3));
+  return v;
+}
 template <typename E>
-__global__ void embed_kernel(const E* __restrict__ emb, const int32_t* __restrict__ tok, float* __restrict__ h,
-                             int rows, int d) {
-  const int64_t total = (int64_t)rows * d;
+static bool emb_aligned(const void* emb) { return (uintptr_t)emb % (4 * sizeof(E)) == 0; }
+
+template <typename E, bool V>
+__global__ __launch_bounds__(256) void embed_kernel(const E* __restrict__ emb, const int32_t* __restrict__ tok,
+                                                    float* __restrict__ h, int rows, int d) {
+  const int n4 = d >> 2;
+  const int64_t total = (int64_t)rows * n4;
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < total; i += (int64_t)gridDim.x * blockDim.x) {
-    const int64_t r = i / d, c = i - r * d;
-    h[i] = Act<E>::load(emb + (int64_t)tok[r] * d + c);
+    const int64_t r = i / n4, c = (i - r * n4) * 4;
+    *reinterpret_cast<float4*>(h + r * d + c) = emb4<E, V>(emb + (int64_t)tok[r] * d + c);
   }
 }
 
 hipError_t launch_embed(const void* emb, bool emb_bf16, const int32_t* tokens, float* h, int rows, int d,
                         hipStream_t s) {
-  const int64_t total = (int64_t)rows * d;
-  int blocks = (int)((total + 255) / 256);
-  if (blocks > 65536) blocks = 65536;
+  if (d & 3) return hipErrorInvalidValue;
+  const int64_t total = (int64_t)rows * (d >> 2);
+  int blocks = (int)std::min<int64_t>((total + 255) / 256, 65536);
   if (blocks < 1) blocks = 1;
-  if (emb_bf16)
-    embed_kernel<bf16_t><<<blocks, 256, 0, s>>>((const bf16_t*)emb, tokens, h, rows, d);
-  else
-    embed_kernel<float><<<blocks, 256, 0, s>>>((const float*)emb, tokens, h, rows, d);
+#define RK_EMBED(E, V) embed_kernel<E, V><<<blocks, 256, 0, s>>>((const E*)emb, tokens, h, rows, d)
+  if (emb_bf16) { if (emb_aligned<bf16_t>(emb)) RK_EMBED(bf16_t, true); else RK_EMBED(bf16_t, false); }
+  else { if (emb_aligned<float>(emb)) RK_EMBED(float, true); else RK_EMBED(float, false); }
+#undef RK_EMBED
   return hipGetLastError();
 }
 
 // Row r of table dst (sequence k, local index j) takes token src.off[k] + pos0 + j.
-template <typename E>
+template <typename E, bool V>
 __global__ void embed_gather_kernel(const E* __restrict__ emb, const int32_t* __restrict__ tok, SeqTable src,
                                     SeqTable dst, int pos0, float* __restrict__ h, int d) {
   for (int r = blockIdx.x; r < dst.rows; r += gridDim.x) {
     const int k = seq_of_row(dst, r);
     const int64_t t = tok[src.off[k] + pos0 + (r - dst.off[k])];
-    for (int c = threadIdx.x; c < d; c += blockDim.x) h[(int64_t)r * d + c] = Act<E>::load(emb + t * d + c);
+    for (int c = threadIdx.x * 4; c < d; c += blockDim.x * 4) {
+      *reinterpret_cast<float4*>(h + (int64_t)r * d + c) = emb4<E, V>(emb + t * d + c);
+    }
   }
 }
 
 hipError_t launch_embed_gather(const void* emb, bool emb_bf16, const int32_t* tokens, const SeqTable& src,
                                const SeqTable& dst, int pos0, float* h, int d, hipStream_t s) {
   if (dst.rows <= 0) return hipSuccess;
+  if (d & 3) return hipErrorInvalidValue;
   const int blocks = std::min(dst.rows, 65536);
-  if (emb_bf16)
-    embed_gather_kernel<bf16_t><<<blocks, 256, 0, s>>>((const bf16_t*)emb, tokens, src, dst, pos0, h, d);
-  else
-    embed_gather_kernel<float><<<blocks, 256, 0, s>>>((const float*)emb, tokens, src, dst, pos0, h, d);
+#define RK_GATHER(E, V) embed_gather_kernel<E, V><<<blocks, 256, 0, s>>>((const E*)emb, tokens, src, dst, pos0, h, d)
+  if (emb_bf16) { if (emb_aligned<bf16_t>(emb)) RK_GATHER(bf16_t, true); else RK_GATHER(bf16_t, false); }
+  else { if (emb_aligned<float>(emb)) RK_GATHER(float, true); else RK_GATHER(float, false); }
+#undef RK_GATHER
   return hipGetLastError();
 }
 
@@ -77,10 +97,13 @@ hipError_t launch_copy_cols(const void* src, int64_t ld_src_bytes, int64_t off_b
 }
 
 // --------------------------------------------------------------------------- RMSNorm
-// One wave per row: out = h / sqrt(mean(h^2) + eps) * g.  fp32 in, act out.  With
-// NV > 0 the row stays in registers (NV float4 per lane) between the sum of
-// squares and the scaled store, and each lane writes its four outputs with one
-// 16-byte (fp32) or 8-byte (bf16) store; NV = 0 streams the row twice (any d).
+// out = h / sqrt(mean(h^2) + eps) * g.  fp32 in, act out.  W waves per row: one, or the
+// four of the workgroup for rows of more than 2048 values (by d alone, so a row's
+// sum does not depend on the number of rows; 16 rows of 4096: 9.7 -> 5 us, many
+// rows are bound by memory either way).  With NV > 0 the row stays in registers (NV
+// float4 per lane) between the sum of squares and the scaled store, and each lane
+// writes its four outputs with one 16-byte (fp32) or 8-byte (bf16) store; NV = 0
+// streams the row twice (any d).
 __device__ __forceinline__ void store4v(float* p, float a, float b, float c, float d) {
   *reinterpret_cast<float4*>(p) = make_float4(a, b, c, d);
 }
@@ -91,67 +114,80 @@ __device__ __forceinline__ void store4v(bf16_t* p, float a, float b, float c, fl
   *reinterpret_cast<uint2*>(p) = u;
 }
 
-template <typename O, int NV>
+template <typename O, int NV, int W>
 __global__ __launch_bounds__(256) void rmsnorm_kernel(const float* __restrict__ h, const float* __restrict__ g,
                                                       O* __restrict__ out, int rows, int d, float eps) {
-  const int lane = threadIdx.x & 63;
-  const int row = blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (row >= rows) return;
+  constexpr int NT = 64 * W;   // threads per row
+  const int t = threadIdx.x % NT;
+  const int row = blockIdx.x * (4 / W) + threadIdx.x / NT;
+  if (row >= rows) return;   // W = 4: the whole workgroup
   const float4* hr = reinterpret_cast<const float4*>(h + (int64_t)row * d);
   const float4* g4 = reinterpret_cast<const float4*>(g);
   O* orow = out + (int64_t)row * d;
   const int n4 = d >> 2;
   float ss = 0.f;
+  float4 v[NV > 0 ? NV : 1];
   if constexpr (NV > 0) {
-    float4 v[NV];
 #pragma unroll
     for (int j = 0; j < NV; ++j) {
-      const int i = lane + 64 * j;
+      const int i = t + NT * j;
       v[j] = i < n4 ? hr[i] : make_float4(0.f, 0.f, 0.f, 0.f);
     }
 #pragma unroll
     for (int j = 0; j < NV; ++j) ss += v[j].x * v[j].x + v[j].y * v[j].y + v[j].z * v[j].z + v[j].w * v[j].w;
+  } else {
+    for (int i = t; i < n4; i += NT) {
+      const float4 x = hr[i];
+      ss += x.x * x.x + x.y * x.y + x.z * x.z + x.w * x.w;
+    }
+  }
 #pragma unroll
-    for (int m = 32; m >= 1; m >>= 1) ss += __shfl_xor(ss, m, 64);
-    const float inv = 1.0f / sqrtf(ss / (float)d + eps);
+  for (int m = 32; m >= 1; m >>= 1) ss += __shfl_xor(ss, m, 64);
+  if constexpr (W > 1) {
+    __shared__ float part[W];
+    if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = ss;
+    __syncthreads();
+    ss = part[0];
+#pragma unroll
+    for (int q = 1; q < W; ++q) ss += part[q];
+  }
+  const float inv = 1.0f / sqrtf(ss / (float)d + eps);
+  if constexpr (NV > 0) {
 #pragma unroll
     for (int j = 0; j < NV; ++j) {
-      const int i = lane + 64 * j;
+      const int i = t + NT * j;
       if (i < n4) {
         const float4 w = g4[i];
         store4v(orow + 4 * i, v[j].x * inv * w.x, v[j].y * inv * w.y, v[j].z * inv * w.z, v[j].w * inv * w.w);
       }
     }
   } else {
-    for (int i = lane; i < n4; i += 64) {
-      const float4 v = hr[i];
-      ss += v.x * v.x + v.y * v.y + v.z * v.z + v.w * v.w;
-    }
-#pragma unroll
-    for (int m = 32; m >= 1; m >>= 1) ss += __shfl_xor(ss, m, 64);
-    const float inv = 1.0f / sqrtf(ss / (float)d + eps);
-    for (int i = lane; i < n4; i += 64) {
-      const float4 v = hr[i], w = g4[i];
-      store4v(orow + 4 * i, v.x * inv * w.x, v.y * inv * w.y, v.z * inv * w.z, v.w * inv * w.w);
+    for (int i = t; i < n4; i += NT) {
+      const float4 x = hr[i], w = g4[i];
+      store4v(orow + 4 * i, x.x * inv * w.x, x.y * inv * w.y, x.z * inv * w.z, x.w * inv * w.w);
     }
   }
 }
 
 template <typename O>
 static void rmsnorm_go(const float* h, const float* g, O* out, int rows, int d, float eps, hipStream_t s) {
-  const int blocks = (rows + 3) / 4;
-  const int nv = (d / 4 + 63) / 64;   // float4 per lane
-  switch (nv) {
-    case 1: rmsnorm_kernel<O, 1><<<blocks, 256, 0, s>>>(h, g, out, rows, d, eps); break;
-    case 2: rmsnorm_kernel<O, 2><<<blocks, 256, 0, s>>>(h, g, out, rows, d, eps); break;
-    case 3: rmsnorm_kernel<O, 3><<<blocks, 256, 0, s>>>(h, g, out, rows, d, eps); break;
-    case 4: rmsnorm_kernel<O, 4><<<blocks, 256, 0, s>>>(h, g, out, rows, d, eps); break;
-    case 5: case 6: rmsnorm_kernel<O, 6><<<blocks, 256, 0, s>>>(h, g, out, rows, d, eps); break;
-    case 7: case 8: rmsnorm_kernel<O, 8><<<blocks, 256, 0, s>>>(h, g, out, rows, d, eps); break;
-    case 9: case 10: case 11: case 12: rmsnorm_kernel<O, 12><<<blocks, 256, 0, s>>>(h, g, out, rows, d, eps); break;
-    case 13: case 14: case 15: case 16: rmsnorm_kernel<O, 16><<<blocks, 256, 0, s>>>(h, g, out, rows, d, eps); break;
-    default: rmsnorm_kernel<O, 0><<<blocks, 256, 0, s>>>(h, g, out, rows, d, eps); break;
+#define RK_NORM(NV, W) rmsnorm_kernel<O, NV, W><<<(rows + 4 / W - 1) / (4 / W), 256, 0, s>>>(h, g, out, rows, d, eps)
+  if (d <= 2048) {
+    const int nv = (d / 4 + 63) / 64;   // float4 per lane
+    if (nv <= 1) RK_NORM(1, 1);
+    else if (nv <= 2) RK_NORM(2, 1);
+    else if (nv <= 3) RK_NORM(3, 1);
+    else if (nv <= 4) RK_NORM(4, 1);
+    else if (nv <= 6) RK_NORM(6, 1);
+    else RK_NORM(8, 1);
+  } else {
+    const int nv = (d / 4 + 255) / 256;
+    if (nv <= 3) RK_NORM(3, 4);
+    else if (nv <= 4) RK_NORM(4, 4);
+    else if (nv <= 8) RK_NORM(8, 4);
+    else RK_NORM(0, 4);
   }
+#undef RK_NORM
 }
 
 hipError_t launch_rmsnorm(const float* h, const float* g, void* out, bool out_bf16, int rows, int d, float eps,

@@ -113,17 +113,33 @@ __global__ __launch_bounds__(256) void lm_lse_kernel(const bf16_t* __restrict__ 
   if ((lane >> 5) == 0 && token < rows) part[(int64_t)chunk * rows + token] = make_float2(mm, zz);
 }
 
-__global__ void lse_merge_kernel(const float2* __restrict__ part, int n_chunks, int rows, float* __restrict__ lse) {
-  const int r = blockIdx.x * blockDim.x + threadIdx.x;
-  if (r >= rows) return;
+// The chunk merges: 16 lanes per row, lane j takes chunks j, j + 16, ... in order, and a
+// fixed butterfly adds the lanes (double).  One thread per row walked all chunks, a
+// serial chain of loads: 64 us for 250 chunks of 509 rows, 526 us for 1002 of 16 rows.
+constexpr int kMergeLanes = 16, kMergeRows = 256 / kMergeLanes;
+
+template <typename T>
+__device__ __forceinline__ T merge_sum(T v) {
+#pragma unroll
+  for (int m = kMergeLanes / 2; m >= 1; m >>= 1) v += __shfl_xor(v, m, 64);
+  return v;
+}
+
+__global__ __launch_bounds__(256) void lse_merge_kernel(const float2* __restrict__ part, int n_chunks, int rows,
+                                                        float* __restrict__ lse) {
+  const int r = blockIdx.x * kMergeRows + threadIdx.x / kMergeLanes, j = threadIdx.x % kMergeLanes;
+  const int rr = min(r, rows - 1);
   float M = -INFINITY;
-  for (int c = 0; c < n_chunks; ++c) M = fmaxf(M, part[(int64_t)c * rows + r].x);
+  for (int c = j; c < n_chunks; c += kMergeLanes) M = fmaxf(M, part[(int64_t)c * rows + rr].x);
+#pragma unroll
+  for (int m = kMergeLanes / 2; m >= 1; m >>= 1) M = fmaxf(M, __shfl_xor(M, m, 64));
   double z = 0.0;
-  for (int c = 0; c < n_chunks; ++c) {
-    const float2 p = part[(int64_t)c * rows + r];
+  for (int c = j; c < n_chunks; c += kMergeLanes) {
+    const float2 p = part[(int64_t)c * rows + rr];
     if (p.y > 0.f) z += (double)p.y * exp((double)p.x - (double)M);
   }
-  lse[r] = (float)((double)M + log(z));
+  z = merge_sum(z);
+  if (j == 0 && r < rows) lse[r] = (float)((double)M + log(z));
 }
 
 // --------------------------------------------------------------------------- fused KL
@@ -321,16 +337,19 @@ __global__ __launch_bounds__(512) void lm_kl_kernel(const bf16_t* __restrict__ X
 }
 
 // kl[g * rows + r] = sum_c T1 + log1p(sum_c S), fixed chunk order, double.
-__global__ void kl_merge_kernel(const float2* __restrict__ part, int n_chunks, int G, int rows, float* __restrict__ kl) {
-  const int r = blockIdx.x * blockDim.x + threadIdx.x, g = blockIdx.y;
-  if (r >= rows) return;
+__global__ __launch_bounds__(256) void kl_merge_kernel(const float2* __restrict__ part, int n_chunks, int G, int rows,
+                                                       float* __restrict__ kl) {
+  const int r = blockIdx.x * kMergeRows + threadIdx.x / kMergeLanes, j = threadIdx.x % kMergeLanes, g = blockIdx.y;
+  const int rr = min(r, rows - 1);
   double t1 = 0.0, s = 0.0;
-  for (int c = 0; c < n_chunks; ++c) {
-    const float2 v = part[((int64_t)c * G + g) * rows + r];
+  for (int c = j; c < n_chunks; c += kMergeLanes) {
+    const float2 v = part[((int64_t)c * G + g) * rows + rr];
     t1 += v.x;
     s += v.y;
   }
-  kl[(int64_t)g * rows + r] = (float)(t1 + log1p(s));
+  t1 = merge_sum(t1);
+  s = merge_sum(s);
+  if (j == 0 && r < rows) kl[(int64_t)g * rows + r] = (float)(t1 + log1p(s));
 }
 
 int lm_chunks(int rows, int vocab) {
@@ -363,7 +382,7 @@ hipError_t launch_lm_lse(const bf16_t* x, const bf16_t* W, int rows, int d, int 
   lm_lse_kernel<<<grid, 256, 0, s>>>(x, W, rows, d, vocab / 128, vt_per_chunk(vocab, chunks), part);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  lse_merge_kernel<<<(rows + 255) / 256, 256, 0, s>>>(part, chunks, rows, lse);
+  lse_merge_kernel<<<(rows + kMergeRows - 1) / kMergeRows, 256, 0, s>>>(part, chunks, rows, lse);
   return hipGetLastError();
 }
 
@@ -390,7 +409,7 @@ hipError_t launch_lm_kl(const bf16_t* xc, const bf16_t* xp, int64_t pass_stride,
     return hipErrorInvalidValue;
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  kl_merge_kernel<<<dim3((rows + 255) / 256, G), 256, 0, s>>>(part, chunks, G, rows, kl);
+  kl_merge_kernel<<<dim3((rows + kMergeRows - 1) / kMergeRows, G), 256, 0, s>>>(part, chunks, G, rows, kl);
   return hipGetLastError();
 }
 
