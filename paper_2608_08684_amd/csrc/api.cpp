@@ -137,8 +137,7 @@ static WsPlan ws_plan(const rk_model* m, int64_t R, int G, uint32_t flags) {
   p.xp = o;       o += align256((size_t)G * Rp * c.d_model * a);
   p.part = o;
   if (m->bf16 && !local) {
-    // lm_chunks(rows) * rows <= min(n_vt * 128 * n_tt, (2048 + n_tt) * 128) and
-    // lm_kl_chunks(rows) * rows <= min(n_vt * 256 * n_tb, (1024 + n_tb) * 256) for rows <= R
+    // a pair per row (lm_lse), and with room lm_kl_chunks(rows) * rows <= min(n_vt * 256 * n_tb, (1024 + n_tb) * 256) for rows <= R
     const size_t n_vt = c.vocab / 128, n_tt = (R + 127) / 128, n_tb = (R + 255) / 256;
     const size_t bound = std::max(std::min(n_vt * 128 * n_tt, (2048 + n_tt) * 128),
                                   std::min(n_vt * 256 * n_tb, (1024 + n_tb) * 256));
@@ -170,6 +169,7 @@ static WsPlan ws_plan(const rk_model* m, int64_t R, int G, uint32_t flags) {
 // Device buffers of one batch, carved from the workspace.
 struct Bufs {
   float* h; void* x; void* qkv; void* att; void* ff; void* xp;
+  size_t act_bytes;   // x .. ff, free between blocks
   float2* part; float* logits_c; float* logits_p; float* kl; float2* rope; int32_t* rope_pos; float* dbatch;
   double* sacc;
   uint64_t* tag;
@@ -183,7 +183,7 @@ static Bufs carve(const WsPlan& p, void* ws) {
   char* b = (char*)ws;
   Bufs u;
   u.h = (float*)(b + p.h); u.x = b + p.x; u.qkv = b + p.qkv; u.att = b + p.att; u.ff = b + p.ff;
-  u.xp = b + p.xp; u.part = (float2*)(b + p.part); u.logits_c = (float*)(b + p.logits_c);
+  u.xp = b + p.xp; u.act_bytes = p.xp - p.x; u.part = (float2*)(b + p.part); u.logits_c = (float*)(b + p.logits_c);
   u.logits_p = (float*)(b + p.logits_p); u.kl = (float*)(b + p.kl); u.rope = (float2*)(b + p.rope);
   u.rope_pos = (int32_t*)(b + p.rope_pos);
   u.dbatch = (float*)(b + p.dbatch); u.sacc = (double*)(b + p.sacc); u.tag = (uint64_t*)(b + p.tag); u.vpert = b + p.vpert; u.cpre = b + p.cpre;
@@ -395,7 +395,7 @@ static rk_status reference_forward(const rk_model* m, const int32_t* tokens, con
   RK_TRY(launch_rmsnorm(last, m->final_norm, cl.xf, m->bf16, (int)R, (int)d, c.rms_eps, s));
   if (m->bf16 && lse) {
     Timed t("lm_lse", s);
-    RK_TRY(launch_lm_lse((const bf16_t*)cl.xf, (const bf16_t*)m->lm_head, (int)R, (int)d, c.vocab, b.part, cl.lse, s));
+    RK_TRY(launch_lm_lse((const bf16_t*)cl.xf, (const bf16_t*)m->lm_head, (int)R, (int)d, c.vocab, b.x, b.act_bytes, b.part, cl.lse, s));
   }
   return RK_OK;
 }
@@ -637,8 +637,8 @@ static rk_status window_reference(const rk_model* m, const int32_t* tokens, cons
   RK_TRY(launch_rmsnorm(h_last ? h_last : b.h, m->final_norm, wn.w.xf, m->bf16, (int)Rw, (int)d, c.rms_eps, s));
   if (!lse) return RK_OK;
   Timed t("lm_lse", s);
-  RK_TRY(launch_lm_lse((const bf16_t*)wn.w.xf, (const bf16_t*)m->lm_head, (int)Rw, (int)d, c.vocab, b.part,
-                       wn.w.lse, s));
+  RK_TRY(launch_lm_lse((const bf16_t*)wn.w.xf, (const bf16_t*)m->lm_head, (int)Rw, (int)d, c.vocab, b.x,
+                       b.act_bytes, b.part, wn.w.lse, s));
   return RK_OK;
 }
 

@@ -378,14 +378,14 @@ __device__ __forceinline__ uint64_t mix64(uint64_t z) {
   return z ^ (z >> 31);
 }
 
-__global__ __launch_bounds__(256) void state_tag_kernel(const int32_t* __restrict__ tok, int64_t rows,
+__global__ __launch_bounds__(1024) void state_tag_kernel(const int32_t* __restrict__ tok, int64_t rows,
                                                         uint64_t magic, uint64_t host, uint64_t* __restrict__ out) {
-  __shared__ uint64_t part[256];
+  __shared__ uint64_t part[1024];
   uint64_t acc = 0;
-  for (int64_t i = threadIdx.x; i < rows; i += 256) acc += mix64(((uint64_t)i << 32) | (uint32_t)tok[i]);
+  for (int64_t i = threadIdx.x; i < rows; i += 1024) acc += mix64(((uint64_t)i << 32) | (uint32_t)tok[i]);
   part[threadIdx.x] = acc;
   __syncthreads();
-  for (int w = 128; w >= 1; w >>= 1) {
+  for (int w = 512; w >= 1; w >>= 1) {
     if ((int)threadIdx.x < w) part[threadIdx.x] += part[threadIdx.x + w];
     __syncthreads();
   }
@@ -397,7 +397,7 @@ __global__ __launch_bounds__(256) void state_tag_kernel(const int32_t* __restric
 
 hipError_t launch_state_tag(const int32_t* tokens, int64_t rows, uint64_t magic, uint64_t host, uint64_t* out,
                             hipStream_t s) {
-  state_tag_kernel<<<1, 256, 0, s>>>(tokens, rows, magic, host, out);
+  state_tag_kernel<<<1, 1024, 0, s>>>(tokens, rows, magic, host, out);
   return hipGetLastError();
 }
 

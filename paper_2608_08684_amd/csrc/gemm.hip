@@ -164,6 +164,15 @@ struct EpiStoreF32 {
   }
 };
 
+// LM head, log-sum-exp only: the tile's logits never leave the registers.  Each row of
+// the tile ends as one (max, sum of e^(x - max)) pair of its BN columns.
+struct EpiLse {
+  static constexpr int out_cols(int BN) { return BN; }
+  static constexpr bool kPaired = false;
+  using stage_t = float;
+  float2* part;   // [column block][rows]
+};
+
 // --------------------------------------------------------------------------- bf16 MFMA kernels
 // Wave layout.  PD: distance in tile columns between the two values an epilogue
 // combines (a rotary pair, gate/up).  A wave with NI = 2 P column blocks (P = 1 or
@@ -282,6 +291,43 @@ __device__ __forceinline__ void tile_epilogue(const f32x16_t (&acc)[G::MI][G::NI
           if (row < M) e.template apply<BN>(row, bn, c0, Cs + r * SP);
         }
     }
+  }
+}
+
+// (max, sum of e^(x - max)) of every row of the tile over its columns; red: the ring's
+// LDS, freed by the caller.
+template <class G>
+__device__ __forceinline__ void tile_lse(const f32x16_t (&acc)[G::MI][G::NI], float2* red, int m0, int bn, int M,
+                                         float2* part, int wm, int wn, int tid) {
+  constexpr float kLog2e = 1.4426950408889634f;
+  constexpr int NWN = G::NWN;
+  const int lane = tid & 63;
+#pragma unroll
+  for (int mi = 0; mi < G::MI; ++mi) {
+    float m = -INFINITY;
+#pragma unroll
+    for (int ni = 0; ni < G::NI; ++ni)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) m = fmaxf(m, acc[mi][ni][i]);
+    m = fmaxf(m, __shfl_xor(m, 32, 64));   // the half-waves hold the same rows
+    float z = 0.f;
+    const float ml = m * kLog2e;
+#pragma unroll
+    for (int ni = 0; ni < G::NI; ++ni)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) z += __builtin_amdgcn_exp2f(fmaf(acc[mi][ni][i], kLog2e, -ml));
+    z += __shfl_xor(z, 32, 64);
+    if (lane < 32) red[(wm * G::WTM + mi * 32 + lane) * NWN + wn] = make_float2(m, z);
+  }
+  __syncthreads();
+  for (int r = tid; r < G::BM; r += G::NT) {
+    if (m0 + r >= M) break;
+    float m = red[r * NWN].x, z = 0.f;
+#pragma unroll
+    for (int q = 1; q < NWN; ++q) m = fmaxf(m, red[r * NWN + q].x);
+#pragma unroll
+    for (int q = 0; q < NWN; ++q) z += red[r * NWN + q].y * __builtin_amdgcn_exp2f((red[r * NWN + q].x - m) * kLog2e);
+    part[(int64_t)bn * M + m0 + r] = make_float2(m, z);
   }
 }
 
@@ -453,7 +499,10 @@ __global__ __launch_bounds__(512) void gemm_alt_kernel(const bf16_t* __restrict_
   }
   if (w < 4) phase_barrier();
   __syncthreads();   // the staging area overlaps the ring
-  tile_epilogue<G, ROUNDS>(acc, smem, m0, bn, M, e, wm, wcol, tid);
+  if constexpr (std::is_same<E, EpiLse>::value)
+    tile_lse<G>(acc, reinterpret_cast<float2*>(smem), m0, bn, M, e.part, wm, wn, tid);
+  else
+    tile_epilogue<G, ROUNDS>(acc, smem, m0, bn, M, e, wm, wcol, tid);
 }
 
 // --------------------------------------------------------------------------- deep-ring kernel
@@ -742,6 +791,18 @@ static hipError_t go(const GemmArgs& a, bool bf16, const E& e, hipStream_t s) {
     if (narrow) return go_ring<float, 64, 32, 4, 6>(a, e, s);
     return go_ring<float, 64, 64, 4, 5>(a, e, s);
   }
+}
+
+int lse_tile_cols(int vocab) { return vocab % 256 == 0 ? 256 : 128; }
+
+hipError_t launch_lse_tiles(const bf16_t* x, const bf16_t* W, int rows, int d, int cols, int tile_cols, float2* part,
+                            hipStream_t s) {
+  GemmArgs a{};
+  a.A = x; a.lda = d; a.B = W; a.ldb = d; a.M = rows; a.N = cols; a.K = d;
+  const EpiLse e{part};
+  if (tile_cols == 256) go_pd<256, 256, 2, 4, 32, EpiLse, false>(a, e, s);
+  else go_pd<256, 128, 4, 2, 32, EpiLse, false>(a, e, s);
+  return hipGetLastError();
 }
 
 hipError_t launch_gemm(const GemmArgs& a, bool bf16, hipStream_t s) {

@@ -40,79 +40,7 @@ __device__ __forceinline__ float kl_f(float x) {
   return (expf(-fmaxf(x, -80.0f)) - 1.0f) + x;
 }
 
-// --------------------------------------------------------------------------- shared tile GEMM
-// acc[vb] (vb = 0..3) = W[v0 + 32 vb + ..] . X[t0 + 32 w + l32]: the 128 x 128 logit
-// tile, transposed, wave w owning tokens 32w..32w+31.  X is padded to whole
-// 128-row tiles by the caller.  Leaves LDS free on return.
-__device__ __forceinline__ void logit_tile(const bf16_t* __restrict__ W, const bf16_t* __restrict__ X, int v0,
-                                           int t0, int d, v4u* As, v4u* Bs, f32x16_t acc[4]) {
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, l32 = lane & 31;
-  TileSrc sw, sx;
-  sw.init(W + (int64_t)v0 * d, d, w, lane);
-  sx.init(X + (int64_t)t0 * d, d, w, lane);
-#pragma unroll
-  for (int vb = 0; vb < 4; ++vb)
-#pragma unroll
-    for (int i = 0; i < 16; ++i) acc[vb][i] = 0.f;
-  const int nk = d / kBK;
-  sw.load<128>(0, As, w);
-  sx.load<128>(0, Bs, w);
-  wait_vmem();
-  __syncthreads();
-  for (int kt = 0; kt < nk; ++kt) {
-    const int cur = kt & 1;
-    if (kt + 1 < nk) {
-      sw.load<128>(kt + 1, As + (cur ^ 1) * 1024, w);
-      sx.load<128>(kt + 1, Bs + (cur ^ 1) * 1024, w);
-    }
-    const v4u* At = As + cur * 1024;
-    const v4u* Bt = Bs + cur * 1024;
-#pragma unroll
-    for (int ks = 0; ks < 4; ++ks) {
-      const bf16x8_t bx = frag(Bt, w * 32 + l32, ks, lane);
-#pragma unroll
-      for (int vb = 0; vb < 4; ++vb)
-        acc[vb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag(At, vb * 32 + l32, ks, lane), bx, acc[vb], 0, 0, 0);
-    }
-    wait_vmem();
-    __syncthreads();
-  }
-}
-
 // --------------------------------------------------------------------------- clean log-sum-exp
-__global__ __launch_bounds__(256) void lm_lse_kernel(const bf16_t* __restrict__ X, const bf16_t* __restrict__ W,
-                                                     int rows, int d, int n_vt, int vt_per_chunk,
-                                                     float2* __restrict__ part) {
-  __shared__ __attribute__((aligned(16))) v4u smem[4096];
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  const int t0 = blockIdx.x * 128, chunk = blockIdx.y;
-  const int vt0 = chunk * vt_per_chunk, vt1 = min(n_vt, vt0 + vt_per_chunk);
-  float m = -INFINITY, z = 0.f;
-  f32x16_t acc[4];
-  for (int vt = vt0; vt < vt1; ++vt) {
-    logit_tile(W, X, vt * 128, t0, d, smem, smem + 2048, acc);
-    float mx = -INFINITY;
-#pragma unroll
-    for (int vb = 0; vb < 4; ++vb)
-#pragma unroll
-      for (int i = 0; i < 16; ++i) mx = fmaxf(mx, acc[vb][i]);
-    const float m_new = fmaxf(m, mx);
-    float sum = 0.f;
-#pragma unroll
-    for (int vb = 0; vb < 4; ++vb)
-#pragma unroll
-      for (int i = 0; i < 16; ++i) sum += expf(acc[vb][i] - m_new);
-    z = z * expf(m - m_new) + sum;
-    m = m_new;
-  }
-  // merge the two half-waves that share a token
-  const float m2 = __shfl_xor(m, 32, 64), z2 = __shfl_xor(z, 32, 64);
-  const float mm = fmaxf(m, m2);
-  const float zz = (mm == -INFINITY) ? 0.f : z * expf(m - mm) + z2 * expf(m2 - mm);
-  const int token = t0 + w * 32 + (lane & 31);
-  if ((lane >> 5) == 0 && token < rows) part[(int64_t)chunk * rows + token] = make_float2(mm, zz);
-}
-
 // The chunk merges: 16 lanes per row, lane j takes chunks j, j + 16, ... in order, and a
 // fixed butterfly adds the lanes (double).  One thread per row walked all chunks, a
 // serial chain of loads: 64 us for 250 chunks of 509 rows, 526 us for 1002 of 16 rows.
@@ -125,21 +53,27 @@ __device__ __forceinline__ T merge_sum(T v) {
   return v;
 }
 
-__global__ __launch_bounds__(256) void lse_merge_kernel(const float2* __restrict__ part, int n_chunks, int rows,
-                                                        float* __restrict__ lse) {
+// Folds n pairs per row into the row's running pair (none yet if `first`); `last`
+// writes the log-sum-exp instead of the pair.
+__global__ __launch_bounds__(256) void lse_merge_kernel(const float2* __restrict__ part, int n, int rows, bool first,
+                                                        bool last, float2* run, float* __restrict__ lse) {
   const int r = blockIdx.x * kMergeRows + threadIdx.x / kMergeLanes, j = threadIdx.x % kMergeLanes;
   const int rr = min(r, rows - 1);
-  float M = -INFINITY;
-  for (int c = j; c < n_chunks; c += kMergeLanes) M = fmaxf(M, part[(int64_t)c * rows + rr].x);
+  const float2 prev = first ? make_float2(-INFINITY, 0.f) : run[rr];
+  float M = prev.x;
+  for (int c = j; c < n; c += kMergeLanes) M = fmaxf(M, part[(int64_t)c * rows + rr].x);
 #pragma unroll
   for (int m = kMergeLanes / 2; m >= 1; m >>= 1) M = fmaxf(M, __shfl_xor(M, m, 64));
-  double z = 0.0;
-  for (int c = j; c < n_chunks; c += kMergeLanes) {
+  double z = j == 0 && prev.y > 0.f ? (double)prev.y * exp((double)prev.x - (double)M) : 0.0;
+  for (int c = j; c < n; c += kMergeLanes) {
     const float2 p = part[(int64_t)c * rows + rr];
     if (p.y > 0.f) z += (double)p.y * exp((double)p.x - (double)M);
   }
   z = merge_sum(z);
-  if (j == 0 && r < rows) lse[r] = (float)((double)M + log(z));
+  if (j == 0 && r < rows) {
+    if (last) lse[r] = (float)((double)M + log(z));
+    else run[r] = make_float2(M, (float)z);
+  }
 }
 
 // --------------------------------------------------------------------------- fused KL
@@ -352,15 +286,6 @@ __global__ __launch_bounds__(256) void kl_merge_kernel(const float2* __restrict_
   if (j == 0 && r < rows) kl[(int64_t)g * rows + r] = (float)(t1 + log1p(s));
 }
 
-int lm_chunks(int rows, int vocab) {
-  const int n_vt = vocab / 128, n_tt = (rows + 127) / 128;
-  int chunks = (2048 + n_tt - 1) / n_tt;
-  if (chunks > n_vt) chunks = n_vt;
-  if (chunks < 1) chunks = 1;
-  const int per = (n_vt + chunks - 1) / chunks;
-  return (n_vt + per - 1) / per;
-}
-
 // chunks of the fused KL kernel: about 1024 workgroups of 256 tokens; chunk c
 // takes vocab tiles [c n_vt / chunks, (c + 1) n_vt / chunks)
 int lm_kl_chunks(int rows, int vocab) {
@@ -369,21 +294,27 @@ int lm_kl_chunks(int rows, int vocab) {
   return chunks > n_vt ? n_vt : (chunks < 1 ? 1 : chunks);
 }
 
-static int vt_per_chunk(int vocab, int chunks) {
-  const int n_vt = vocab / 128;
-  return (n_vt + chunks - 1) / chunks;
-}
-
-hipError_t launch_lm_lse(const bf16_t* x, const bf16_t* W, int rows, int d, int vocab, float2* part, float* lse,
-                         hipStream_t s) {
+// The logits of the column blocks run on the projections' 8-wave tiles (EpiLse), their
+// pairs are merged per row.  The scratch holds the pairs of `fit` column blocks; a
+// larger vocabulary goes in several launches.  Bound: the matrix cores.  Against tiles
+// of 128 tokens that waited on every k-step: 22636 rows, d = 4096, V = 32000 7.85 ms (0.76
+// PFLOP/s) -> 4.5, 16384 rows, d = 768 1.03 -> 0.75 ms.
+hipError_t launch_lm_lse(const bf16_t* x, const bf16_t* W, int rows, int d, int vocab, void* scratch,
+                         size_t scratch_bytes, float2* run, float* lse, hipStream_t s) {
   if (rows <= 0) return hipSuccess;
-  const int chunks = lm_chunks(rows, vocab);
-  dim3 grid((rows + 127) / 128, chunks);
-  lm_lse_kernel<<<grid, 256, 0, s>>>(x, W, rows, d, vocab / 128, vt_per_chunk(vocab, chunks), part);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  lse_merge_kernel<<<(rows + kMergeRows - 1) / kMergeRows, 256, 0, s>>>(part, chunks, rows, lse);
-  return hipGetLastError();
+  const int cols = lse_tile_cols(vocab), n = vocab / cols;
+  const int64_t fit = (int64_t)(scratch_bytes / ((size_t)rows * sizeof(float2)));
+  if (fit < 1 || d % 64 != 0 || vocab % 128 != 0) return hipErrorInvalidValue;
+  float2* part = (float2*)scratch;
+  for (int b = 0; b < n;) {
+    const int nb = (int)(fit < n - b ? fit : n - b);
+    hipError_t e = launch_lse_tiles(x, W + (int64_t)b * cols * d, rows, d, nb * cols, cols, part, s);
+    if (e != hipSuccess) return e;
+    lse_merge_kernel<<<(rows + kMergeRows - 1) / kMergeRows, 256, 0, s>>>(part, nb, rows, b == 0, b + nb == n, run, lse);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+    b += nb;
+  }
+  return hipSuccess;
 }
 
 hipError_t launch_lm_kl(const bf16_t* xc, const bf16_t* xp, int64_t pass_stride, int G, const bf16_t* W, int rows,

@@ -46,53 +46,13 @@ __device__ __forceinline__ int swz(int row) {
   return CH == 8 ? ((row >> 1) & 7) : ((row >> 2) & 3);
 }
 
-// Per-lane source of a BR x BK tile whose rows start at `rows0` (row stride ld
-// elements).  One wave instruction fills 64 consecutive slots = 64 / CH rows;
-// round j of wave w covers rows (NW j + w) * (64 / CH) ...  The copies are
-// buffer_load_dwordx4 ... lds with the tile's base in an SGPR descriptor, a
-// per-lane 32-bit offset fixed at init, and the k-step and round in the scalar
-// offset, so issuing one costs no vector ALU work.  They are inline assembly:
-// the compiler neither counts them in its own waits nor orders later LDS reads
-// behind them, so callers wait with s_waitcnt vmcnt and a barrier themselves.
-template <int BK = kBK, int NW = 4>
-struct TileSrcT {
-  static constexpr int CH = BK / 8;
-  static constexpr int RPI = 64 / CH;  // rows per wave instruction
-  i32x4_t rsrc;
-  uint32_t voff;
-  int32_t round_bytes;
-  __device__ __forceinline__ void init(const bf16_t* rows0, int64_t ld, int w, int lane) {
-    const int r = w * RPI + lane / CH;
-    const int kc = (lane % CH) ^ swz<CH>(r);   // rounds add multiples of 16 rows: same swizzle
-    const uint64_t base = (uint64_t)rows0;
-    rsrc[0] = __builtin_amdgcn_readfirstlane((int32_t)(uint32_t)base);
-    rsrc[1] = __builtin_amdgcn_readfirstlane((int32_t)(uint32_t)(base >> 32));
-    rsrc[2] = -1;            // no range limit: callers keep every row readable
-    rsrc[3] = 0x00020000;    // raw buffer, 32-bit data format (gfx9 word 3)
-    voff = (uint32_t)(r * ld * 2 + kc * 16);
-    round_bytes = __builtin_amdgcn_readfirstlane((int32_t)(NW * RPI * ld * 2));
-  }
-  // round j (j < BR * CH / (64 NW)) of k-step kt into the tile at dst
-  __device__ __forceinline__ void load_round(int kt, int j, v4u* dst, int w) const {
-    const uint32_t lds = __builtin_amdgcn_readfirstlane(
-        (uint32_t)(uintptr_t)(__attribute__((address_space(3))) v4u*)(dst + (j * NW + w) * 64));
-    const int32_t soff = __builtin_amdgcn_readfirstlane(kt * (BK * 2) + j * round_bytes);
-    asm volatile("s_nop 0\n\tbuffer_load_dwordx4 %0, %1, %2 offen lds"
-                 :
-                 : "v"(voff), "s"(rsrc), "s"(soff), "{m0}"(lds)
-                 : "memory");
-  }
-  // issue the k-step kt of a BR-row tile (NW waves, BR * CH / (64 NW) rounds)
-  template <int BR>
-  __device__ __forceinline__ void load(int kt, v4u* dst, int w) const {
-    static_assert(BR * CH % (64 * NW) == 0, "tile rows must fill whole rounds");
-#pragma unroll
-    for (int j = 0; j < BR * CH / (64 * NW); ++j) load_round(kt, j, dst, w);
-  }
-};
-typedef TileSrcT<kBK, 4> TileSrc;
-
-// Copies of single 8-row groups of a 64-wide k-step (128-byte rows, CH = 8): one
+// The copies are buffer_load_dwordx4 ... lds with the rows' base in an SGPR
+// descriptor, a per-lane 32-bit offset fixed at init, and the k-step in the scalar
+// offset, so issuing one costs no vector ALU work.  They are inline assembly: the
+// compiler neither counts them in its own waits nor orders later LDS reads behind
+// them, so callers wait with s_waitcnt vmcnt and a barrier themselves.
+//
+// Copies of single 8-row groups of a 128-byte k-step (64 bf16 or 32 fp32 values): one
 // wave instruction fills the 64 slots of group g, rows 8 g .. 8 g + 7 from the
 // tile's first row.  The groups a wave copies all have the parity of its index w,
 // so the swizzle of its lanes is fixed at init.

@@ -131,10 +131,16 @@ hipError_t launch_attention(const void* qkv, int64_t ldq, void* out, int64_t ldo
                             const KvPrefix* prefix = nullptr);
 
 // Clean log-sum-exp of the LM head, fused (bf16): lse[r] = logsumexp_v (x[r] . W[v]).
-int lm_chunks(int rows, int vocab);      // vocab chunks of lm_lse (partials: chunks * rows float2)
+// scratch: scratch_bytes of workspace for the (max, sum) pairs of the column blocks, at
+// least 8 bytes per row; run: rows float2.  x holds whole 256-row tiles.
 int lm_kl_chunks(int rows, int vocab);   // vocab chunks of lm_kl (partials: chunks * G * rows float2)
-hipError_t launch_lm_lse(const bf16_t* x, const bf16_t* W, int rows, int d, int vocab, float2* part,
-                         float* lse, hipStream_t s);
+hipError_t launch_lm_lse(const bf16_t* x, const bf16_t* W, int rows, int d, int vocab, void* scratch,
+                         size_t scratch_bytes, float2* run, float* lse, hipStream_t s);
+// part[b * rows + r] = (max, sum of e^(logit - max)) of row r over columns [b C, b C + C) of the
+// cols rows of W, C = tile_cols (256 or 128, a divisor of cols).
+int lse_tile_cols(int vocab);
+hipError_t launch_lse_tiles(const bf16_t* x, const bf16_t* W, int rows, int d, int cols, int tile_cols, float2* part,
+                            hipStream_t s);
 // Fused LM head + KL (bf16): for pass g, kl[g][r] = KL(softmax(x_c W^T) || softmax(x_g W^T)).
 hipError_t launch_lm_kl(const bf16_t* xc, const bf16_t* xp, int64_t pass_stride, int G, const bf16_t* W,
                         int rows, int d, int vocab, const float* lse, float2* part, float* kl,

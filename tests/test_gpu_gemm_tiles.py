@@ -167,3 +167,38 @@ def test_rows_do_not_depend_on_the_batch():
 def test_fp32_block(m, lengths):
     m.dtype = "f32"
     check_block(m, lengths, tol=2e-6, big=2e-5)
+
+
+# the clean log-sum-exp: 128- and 256-wide column blocks, ragged rows, and a vocabulary whose pairs do not fit the
+# scratch of a narrow model at once (several launches).  Logits are fp32 sums of d bf16 products (|x| |w| near 1 each, so
+# off by about 1e-6); log-sum-exp passes that on and rounds once to fp32 (|lse| up to 12: 5e-7)
+@pytest.mark.parametrize("d, vocab, lengths", [(256, 384, [1]), (256, 512, [300, 7]), (128, 128128, [513]),
+                                               (128, 81920, [40, 1000])])
+def test_clean_log_sum_exp(d, vocab, lengths):
+    import torch
+    import paper_2608_08684_amd as rk
+    m = Shape(d, 2, 1, 64, 64, vocab=vocab)
+    g = torch.Generator(device="cuda").manual_seed(7)
+    mat = lambda r, c: torch.empty(r, c, device="cuda", dtype=torch.bfloat16).normal_(0, c ** -0.5, generator=g)
+    one = torch.ones(d, device="cuda")
+    w = {"tok_emb": mat(vocab, d), "lm_head": mat(vocab, d), "final_norm": one, "attn_norm": [one] * 2,
+         "mlp_norm": [one] * 2, "w_qkv": [mat(256, d)] * 2, "w_o": [mat(d, 128)] * 2, "w_gate_up": [mat(128, d)] * 2,
+         "w_down": [mat(d, 64)] * 2}
+    offs = [0]
+    for t in lengths:
+        offs.append(offs[-1] + t)
+    rows = offs[-1]
+    model = rk.Model(m, w)
+    batch = rk.Batch(torch.randint(0, vocab, (rows,), device="cuda", generator=g, dtype=torch.int32), offs)
+    state = torch.full((model.clean_state_size(rows),), 0xFF, dtype=torch.uint8, device="cuda")
+    ws = torch.full((model.workspace_size(rows, 1, 0),), 0xFF, dtype=torch.uint8, device="cuda")
+    model.reference_forward(batch, state, ws)
+    up = lambda n: (n + 255) // 256 * 256
+    x0 = up(2 * rows * d * 4)
+    l0 = x0 + up(up(rows) * d * 2)
+    x = state[x0:x0 + rows * d * 2].view(torch.bfloat16).view(rows, d).double()
+    lse = state[l0:l0 + rows * 4].view(torch.float32).double()
+    want = torch.logsumexp(x @ w["lm_head"].double().t(), dim=1)
+    err = (lse - want).abs().max().item()
+    print(f"d {d} vocab {vocab} rows {rows}: log-sum-exp off by {err:.2e}")
+    assert err < 1e-5
