@@ -523,9 +523,10 @@ static rk_status local_pass(const rk_model* m, const int32_t* tokens, const SeqT
 }
 
 // KL at every position for G passes whose final hidden states sit at xp (stride R*d).
-// Unfused: the clean logits must already be in logits_c; pass logits go to lp.
+// Unfused: the clean logits go to (with_clean), or must already be in, logits_c; pass
+// logits go to lp.
 static rk_status score_group(const rk_model* m, const SeqTable& st, const Clean& cl, const void* xp, int G,
-                             bool unfused, float* lp, float* kl, const Bufs& b, hipStream_t s) {
+                             bool unfused, bool with_clean, float* lp, float* kl, const Bufs& b, hipStream_t s) {
   const rk_model_config& c = m->cfg;
   const int64_t R = st.rows, d = c.d_model;
   if (!unfused) {
@@ -539,6 +540,10 @@ static rk_status score_group(const rk_model* m, const SeqTable& st, const Clean&
     a.A = (const char*)xp + (size_t)g * pad_rows(R) * d * act_bytes(m); a.lda = d; a.B = m->lm_head; a.ldb = d;
     a.M = (int)R; a.N = c.vocab; a.K = (int)d; a.epi = Epi::kStoreF32;
     a.out = lp + (size_t)g * R * c.vocab; a.ldo = c.vocab;
+    if (g == 0 && with_clean) {   // both in one launch: few rows read the LM head's weights once
+      a.A2 = a.A; a.out2 = a.out;
+      a.A = cl.xf; a.out = b.logits_c;
+    }
     Timed t("lm_logits", s);
     RK_TRY(launch_gemm(a, m->bf16, s));
   }
@@ -1316,7 +1321,7 @@ static rk_status profile_run(const rk_model* m, const rk_batch* calib, const int
         }
         if (!local && (e = window_group_final(m, pst, wst, wn, G, glay, galpha, p, max_rows, b.xp, b, s)) != RK_OK)
           return e;
-        if (!local && (e = score_group(m, wst, wn.w, b.xp, G, unfused, b.logits_p, b.kl, b, s)) != RK_OK) return e;
+        if (!local && (e = score_group(m, wst, wn.w, b.xp, G, unfused, false, b.logits_p, b.kl, b, s)) != RK_OK) return e;
         RK_TRY(launch_window_mean(b.kl, Rw, G, wst, 0, b.dbatch, s));
         RK_TRY(launch_accumulate(b.dbatch, st.n, pm, d_out, b.sacc, s));
       }
@@ -1346,7 +1351,7 @@ static rk_status profile_run(const rk_model* m, const rk_batch* calib, const int
       }
       if (!local && (e = resumed_group_final(m, tokens, st, cl, G, glay, galpha, p, max_rows, b.xp, b, s)) != RK_OK)
         return e;
-      if (!local && (e = score_group(m, st, cl, b.xp, G, unfused, b.logits_p, b.kl, b, s)) != RK_OK) return e;
+      if (!local && (e = score_group(m, st, cl, b.xp, G, unfused, false, b.logits_p, b.kl, b, s)) != RK_OK) return e;
       RK_TRY(launch_window_mean(b.kl, R, G, st, p->window_start, b.dbatch, s));
       RK_TRY(launch_accumulate(b.dbatch, st.n, pm, d_out, b.sacc, s));
     }
@@ -1675,9 +1680,8 @@ static rk_status score_window(const rk_model* m, const WinCall& c, int G, float*
   rk_status e;
   float* kl = kl_pos ? kl_pos : c.b.kl;
   const bool unfused = logits_out != nullptr;
-  if (unfused && (e = clean_logits(m, c.wst, c.wn.w, c.b.logits_c, c.s)) != RK_OK) return e;
-  if ((e = score_group(m, c.wst, c.wn.w, c.b.xp, G, unfused, unfused ? logits_out : c.b.logits_p, kl, c.b, c.s)) !=
-      RK_OK)
+  if ((e = score_group(m, c.wst, c.wn.w, c.b.xp, G, unfused, true, unfused ? logits_out : c.b.logits_p, kl, c.b,
+                       c.s)) != RK_OK)
     return e;
   RK_TRY(launch_window_mean(kl, c.wst.rows, G, c.wst, 0, d_out, c.s));
   return RK_OK;
@@ -1860,8 +1864,8 @@ rk_status rk_profile_layer(const rk_model* m, const rk_batch* batch, int32_t lay
       if ((e = window_local_pass(m, pst, wst, wn, layer, alpha, p, h_last, kl, b, s)) != RK_OK) return e;
     } else {
       if ((e = window_perturbed_final(m, pst, wst, wn, layer, alpha, p, b.xp, b, s)) != RK_OK) return e;
-      if (unfused && (e = clean_logits(m, wst, wn.w, b.logits_c, s)) != RK_OK) return e;
-      if ((e = score_group(m, wst, wn.w, b.xp, 1, unfused, logits_out ? logits_out : b.logits_p, kl, b, s)) != RK_OK)
+      if ((e = score_group(m, wst, wn.w, b.xp, 1, unfused, true, logits_out ? logits_out : b.logits_p, kl, b, s)) !=
+          RK_OK)
         return e;
     }
     RK_TRY(launch_window_mean(kl, wst.rows, 1, wst, 0, d_out, s));
@@ -1888,8 +1892,7 @@ rk_status rk_profile_layer(const rk_model* m, const rk_batch* batch, int32_t lay
     if ((e = local_pass(m, batch->tokens, st, cl, layer, alpha, p, h_last, kl, b, s)) != RK_OK) return e;
   } else {
     if ((e = perturbed_final(m, batch->tokens, st, cl, layer, alpha, p, b.xp, b, s)) != RK_OK) return e;
-    if (unfused && (e = clean_logits(m, st, cl, b.logits_c, s)) != RK_OK) return e;
-    if ((e = score_group(m, st, cl, b.xp, 1, unfused, logits_out ? logits_out : b.logits_p, kl, b, s)) != RK_OK)
+    if ((e = score_group(m, st, cl, b.xp, 1, unfused, true, logits_out ? logits_out : b.logits_p, kl, b, s)) != RK_OK)
       return e;
   }
   RK_TRY(launch_window_mean(kl, st.rows, 1, st, p->window_start, d_out, s));

@@ -149,6 +149,7 @@ struct EpiStoreF32 {
   static constexpr int out_cols(int BN) { return BN; }
   static constexpr bool kPaired = false;
   float* out; int64_t ldo;
+  float* out2;   // output of the second rows (GemmArgs.A2)
   using stage_t = float;
   template <int HB>
   __device__ __forceinline__ ColRuns runs(int bn, int) const {
@@ -526,9 +527,9 @@ __global__ __launch_bounds__(512) void gemm_alt_kernel(const bf16_t* __restrict_
 // with a 64x128 tile: 1801 rows, N = 32000, K = 768 73 TFLOP/s, N = 768, K = 3072 28;
 // 256 rows, N = 256, K = 1024 97 us.
 template <typename T, int BM, int BN, int NW, int S, class E>
-__global__ __launch_bounds__(64 * NW) void gemm_ring_kernel(const T* __restrict__ A, int64_t lda,
-                                                            const T* __restrict__ B, int64_t ldb, int M, int K,
-                                                            int d_ff, int n_bn, E e) {
+__global__ __launch_bounds__(64 * NW) void gemm_ring_kernel(const T* __restrict__ A, const T* __restrict__ A2,
+                                                            int64_t lda, const T* __restrict__ B, int64_t ldb, int M,
+                                                            int K, int d_ff, int n_bn, E e) {
   constexpr bool F32 = sizeof(T) == 4;
   constexpr int GW = (BM / 32) * (BN / 32), NT = 64 * NW, HB = BN / 2, CH = 8;
   constexpr int SA = BM * CH, SS = (BM + BN) * CH;   // 16-byte slots of a stage's A tile, of a stage
@@ -541,8 +542,15 @@ __global__ __launch_bounds__(64 * NW) void gemm_ring_kernel(const T* __restrict_
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = w / (BN / 32), wn = w % (BN / 32);
   int bm_, bn;
-  const int n_bm = (M + BM - 1) / BM;
-  xcd_tile((int)blockIdx.x, n_bm, n_bn, n_bm, &bm_, &bn);   // the row tiles of one column block together
+  const int n_bm = (M + BM - 1) / BM, n_m = A2 ? 2 * n_bm : n_bm;
+  xcd_tile((int)blockIdx.x, n_m, n_bn, n_m, &bm_, &bn);   // the row tiles of one column block together
+  if constexpr (std::is_same<E, EpiStoreF32>::value) {
+    if (bm_ >= n_bm) {   // the second rows
+      bm_ -= n_bm;
+      A = A2;
+      e.out = e.out2;
+    }
+  }
   const int m0 = bm_ * BM;
   const ColRuns cr = e.template runs<HB>(bn, d_ff);
   // this wave's 8-row groups: from A, or from either run of B
@@ -733,8 +741,8 @@ static Tile pick_tile(const GemmArgs& a, bool swiglu) {
 template <typename T, int BM, int BN, int NW, int S, class E>
 static hipError_t go_ring(const GemmArgs& a, const E& e, hipStream_t s) {
   const int nbn = a.N / BN;
-  gemm_ring_kernel<T, BM, BN, NW, S, E><<<(a.M + BM - 1) / BM * nbn, 64 * NW, 0, s>>>(
-      (const T*)a.A, a.lda, (const T*)a.B, a.ldb, a.M, a.K, a.d_ff, nbn, e);
+  gemm_ring_kernel<T, BM, BN, NW, S, E><<<(a.M + BM - 1) / BM * nbn * (a.A2 ? 2 : 1), 64 * NW, 0, s>>>(
+      (const T*)a.A, (const T*)a.A2, a.lda, (const T*)a.B, a.ldb, a.M, a.K, a.d_ff, nbn, e);
   return hipGetLastError();
 }
 
@@ -771,7 +779,20 @@ template <class E, bool SWIGLU>
 static hipError_t go(const GemmArgs& a, bool bf16, const E& e, hipStream_t s) {
   if (bf16) {
     if (E::kPaired && !SWIGLU && a.head_dim != 64 && a.head_dim != 128) return hipErrorInvalidValue;
-    switch (pick_tile(a, SWIGLU)) {
+    const Tile tile = pick_tile(a, SWIGLU);
+    // the 8-wave tiles take the second rows (the LM head only) in a launch of their own
+    if (a.A2 && tile != Tile::k32x64 && tile != Tile::k32x32 && tile != Tile::k64x64 && tile != Tile::k64x128) {
+      if constexpr (std::is_same<E, EpiStoreF32>::value) {
+        GemmArgs one = a;
+        one.A2 = nullptr;
+        hipError_t r = go<E, SWIGLU>(one, true, e, s);
+        if (r != hipSuccess) return r;
+        one.A = a.A2;
+        return go<E, SWIGLU>(one, true, EpiStoreF32{e.out2, e.ldo, nullptr}, s);
+      }
+      return hipErrorInvalidValue;
+    }
+    switch (tile) {
       case Tile::k32x64: return go_ring<bf16_t, 32, 64, 4, 6>(a, e, s);
       case Tile::k32x32: return go_ring<bf16_t, 32, 32, 4, 9>(a, e, s);
       case Tile::k64x64: return go_ring<bf16_t, 64, 64, 4, 5>(a, e, s);
@@ -807,6 +828,7 @@ hipError_t launch_lse_tiles(const bf16_t* x, const bf16_t* W, int rows, int d, i
 
 hipError_t launch_gemm(const GemmArgs& a, bool bf16, hipStream_t s) {
   if (a.M <= 0) return hipSuccess;
+  if (a.A2 && a.epi != Epi::kStoreF32) return hipErrorInvalidValue;
   switch (a.epi) {
     case Epi::kStoreRope:
       if (bf16) {
@@ -829,7 +851,7 @@ hipError_t launch_gemm(const GemmArgs& a, bool bf16, hipStream_t s) {
         return go<EpiSwiGLU<float>, true>(a, false, e, s);
       }
     case Epi::kStoreF32: {
-      EpiStoreF32 e{(float*)a.out, a.ldo};
+      EpiStoreF32 e{(float*)a.out, a.ldo, (float*)a.out2};
       return go<EpiStoreF32, false>(a, bf16, e, s);
     }
   }

@@ -103,6 +103,7 @@ struct GemmArgs {
   // rotation, before rounding (q_cols = 0: no scaling)
   int q_cols; float q_scale;
   int d_ff;                        // kSwiGLU: gate rows [0, d_ff), up rows [d_ff, 2 d_ff)
+  const void* A2; void* out2;      // kStoreF32: M more rows, out2 = A2 * B^T (NULL: none)
 };
 hipError_t launch_gemm(const GemmArgs& a, bool bf16, hipStream_t s);
 
