@@ -12,7 +12,7 @@
 //              (ties to the lower position), in increasing order;
 //   the compressed cache holds those positions' rotated Keys and Values.
 //
-// Kernels (one layer per launch):
+// Kernels (all layers per launch):
 //   snap_stats_kernel   per (key chunk, KV head, sequence): running max / sum of
 //                       exp2 of the observation queries' scores over the chunk's
 //                       keys (S^T = K Q^T on MFMA, one query per lane);
@@ -21,7 +21,7 @@
 //                       with the accumulator started at -c_t, so exp2 of the
 //                       result is the probability; each lane owns one key and
 //                       sums its probabilities over queries and heads;
-//   snap_select_kernel  per (KV head, sequence): pooling into LDS, radix select
+//   snap_select_kernel  per (KV head, sequence, layer): pooling into LDS, radix select
 //                       of the (b - w)-th largest pooled vote, compaction in
 //                       position order, gather of the K and V rows.
 // Queries arrive multiplied by log2(e) / sqrt(d_h) (the attention kernels' form),
@@ -318,14 +318,30 @@ __global__ __launch_bounds__(kSelThreads) void snap_select_kernel(
         if ((x & mask) == prefix) atomicAdd(&hist[(x >> shift) & 255], 1);
       }
       __syncthreads();
-      if (tid == 0) {
-        int cum = 0, d = 255;
-        for (; d > 0; --d) {
-          if (cum + hist[d] >= rem) break;
-          cum += hist[d];
+      // the largest digit d with hist[d] + ... + hist[255] >= rem (0 if none), by one wave: lane l
+      // holds digits 255 - 4 l .. 252 - 4 l (one thread walking the bins took a quarter of
+      // the kernel)
+      if (tid < 64) {
+        int h[4], own = 0;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          h[j] = hist[255 - 4 * tid - j];
+          own += h[j];
         }
-        bcast[0] = d;
-        bcast[1] = rem - cum;
+        int incl = own;
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1) {
+          const int v = __shfl_up(incl, off, 64);
+          if (tid >= off) incl += v;
+        }
+        const uint64_t reach = __ballot(incl >= rem);
+        const int first = reach ? __builtin_ctzll(reach) : 63;
+        if (tid == first) {
+          int cum = incl - own, j = 0;
+          while (j < 3 && cum + h[j] < rem) cum += h[j++];
+          bcast[0] = 255 - 4 * tid - j;
+          bcast[1] = rem - cum;
+        }
       }
       __syncthreads();
       prefix |= (uint32_t)bcast[0] << shift;
@@ -358,12 +374,28 @@ __global__ __launch_bounds__(kSelThreads) void snap_select_kernel(
   // gather the retained rows' Keys and Values
   constexpr int CH = DH / 8;
   const int64_t voff = (int64_t)n_kv * DH;
-  for (int idx = tid; idx < keep * CH; idx += kSelThreads) {
-    const int j = idx / CH, ch = idx % CH;
-    const int p = min(max(positions[e0 + j], 0), T - 1);   // always a row of this sequence
-    const bf16_t* src = kv + (int64_t)(row0 + p) * ldkv + (int64_t)g * DH + ch * 8;
-    *reinterpret_cast<v4u*>(k_out + (e0 + j) * DH + ch * 8) = *reinterpret_cast<const v4u*>(src);
-    *reinterpret_cast<v4u*>(v_out + (e0 + j) * DH + ch * 8) = *reinterpret_cast<const v4u*>(src + voff);
+  // U chunks of a thread in flight: with one workgroup per CU a single one leaves the
+  // copy waiting on its latency (8 layers of 4 x 8192 keys, 8 KV heads of 128, a fifth kept:
+  // 174 -> 134 us with the digit search above)
+  constexpr int U = 4;
+  for (int i0 = tid; i0 < keep * CH; i0 += U * kSelThreads) {
+    v4u kk[U], vv[U];
+#pragma unroll
+    for (int q = 0; q < U; ++q) {
+      const int idx = min(i0 + q * kSelThreads, keep * CH - 1), j = idx / CH, ch = idx % CH;
+      const int p = min(max(positions[e0 + j], 0), T - 1);   // always a row of this sequence
+      const bf16_t* src = kv + (int64_t)(row0 + p) * ldkv + (int64_t)g * DH + ch * 8;
+      kk[q] = *reinterpret_cast<const v4u*>(src);
+      vv[q] = *reinterpret_cast<const v4u*>(src + voff);
+    }
+#pragma unroll
+    for (int q = 0; q < U; ++q) {
+      const int idx = i0 + q * kSelThreads, j = idx / CH, ch = idx % CH;
+      if (idx < keep * CH) {
+        *reinterpret_cast<v4u*>(k_out + (e0 + j) * DH + ch * 8) = kk[q];
+        *reinterpret_cast<v4u*>(v_out + (e0 + j) * DH + ch * 8) = vv[q];
+      }
+    }
   }
 }
 
