@@ -107,7 +107,8 @@ struct AttnTraits {
 template <int DH, bool PREFIX>
 __global__ __launch_bounds__(64 * AttnTraits<DH>::kWaves, AttnTraits<DH>::kMinBlocks) void attn_bf16_kernel(const bf16_t* __restrict__ qkv, int64_t ldq,
                                                         bf16_t* __restrict__ out, int64_t ldo, SeqTable st,
-                                                        AttnWork wk, int H, int Hkv, int n_items, KvPrefix pk) {
+                                                        AttnWork wk, int H, int Hkv, int n_items, int paired,
+                                                        KvPrefix pk) {
   constexpr int NW = AttnTraits<DH>::kWaves;
   constexpr int BQ = 32 * NW, BKV = 64;
   constexpr int CH = DH / 8;                // 16-byte chunks per row
@@ -227,8 +228,8 @@ __global__ __launch_bounds__(64 * AttnTraits<DH>::kWaves, AttnTraits<DH>::kMinBl
 
   const bf16x2_t ones = {(__bf16)1.0f, (__bf16)1.0f};
   // causal rows: the pair (nqb - 1 - x, x); behind a cached prefix every q-block
-  // costs about the same, so one q-block per item
-  const int n_blocks = PREFIX ? 1 : ((x == nqb - 1 - x) ? 1 : 2);
+  // costs about the same, so one q-block per item; also where the pairs leave CUs idle
+  const int n_blocks = PREFIX || !paired ? 1 : ((x == nqb - 1 - x) ? 1 : 2);
   for (int bi = 0; bi < n_blocks; ++bi) {
     const int qb = (PREFIX || bi == 0) ? nqb - 1 - x : x;
     const int q0 = qb * BQ;
@@ -524,10 +525,16 @@ hipError_t launch_attention(const void* qkv, int64_t ldq, void* out, int64_t ldo
   if (bf16) {
     const bool pre = prefix && prefix->P > 0;
     const int bq = 32 * (head_dim == 64 ? AttnTraits<64>::kWaves : AttnTraits<128>::kWaves);   // queries per block
-    // items = pairs of q-blocks, or single q-blocks behind a cached prefix
+    // Items = pairs of q-blocks.  Single q-blocks behind a cached prefix, and where all
+    // single blocks run at once (one workgroup on each of 256 CUs): a pair's second block only
+    // adds to the longest item's time (509 rows, 12 heads of 64: 24 pairs of up to 10 tiles
+    // 14.1 us, 48 blocks of up to 8 tiles 10.8).
+    int64_t blocks = 0;
+    for (int k = 0; k < st.n; ++k) blocks += (st.off[k + 1] - st.off[k] + bq - 1) / bq;
+    const bool paired = !pre && blocks * n_heads > 256;
     const AttnWork wk = attn_work(st, [&](int len) {
       const int nqb = (len + bq - 1) / bq;
-      return pre ? nqb : (nqb + 1) / 2;
+      return paired ? (nqb + 1) / 2 : nqb;
     });
     if (wk.total == 0) return hipSuccess;
     // the buffer descriptor covers one sequence's rows with 32-bit byte offsets
@@ -545,7 +552,7 @@ hipError_t launch_attention(const void* qkv, int64_t ldq, void* out, int64_t ldo
     }
 #define RK_ATTN(D, PRE)                                                                                      \
   attn_bf16_kernel<D, PRE><<<grid, 64 * AttnTraits<D>::kWaves, 0, s>>>((const bf16_t*)qkv, ldq, (bf16_t*)out, ldo, \
-                                                                      st, wk, n_heads, n_kv_heads, n_items, pk)
+                                                                      st, wk, n_heads, n_kv_heads, n_items, paired ? 1 : 0, pk)
     if (head_dim == 128) { if (pre) RK_ATTN(128, true); else RK_ATTN(128, false); }
     else if (head_dim == 64) { if (pre) RK_ATTN(64, true); else RK_ATTN(64, false); }
     else return hipErrorInvalidValue;
