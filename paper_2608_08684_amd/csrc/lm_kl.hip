@@ -87,8 +87,13 @@ __global__ __launch_bounds__(256) void lse_merge_kernel(const float2* __restrict
 // then the G perturbed tiles against the same W rows, folding each into the
 // per-lane (T1, S) of its pass.  All the k-steps of all these tiles form one
 // stream through a 3-stage LDS ring, so the copies run ahead across tile
-// boundaries.  Wave w owns tokens 32 w .. 32 w + 31 (the MFMA N side) and all 128
-// vocab rows of the tile (M side): its reductions over vocab stay in its lanes.
+// boundaries.  Wave w owns 64 tokens (64 (w / 2) .., the MFMA N side) and 64 vocab rows
+// of the tile (half w % 2, M side): four fragments per four MFMAs, where 128 rows x 32
+// tokens take five; its reductions over vocab stay in its lanes until the two halves
+// meet at the end.  Measured against that: d = 4096, V = 32000, 32768 tokens, one pass 16.3
+// -> 15.6 ms; d = 768, 16384 tokens, 12 passes 11.2 -> 11.0 ms.  Bound: the copies (48 KB
+// per 1024 MFMA cycles) and their latency; the projections' alternating schedule, whose
+// copies have two phases to land here instead of four, was slower (19.8 and 12.7 ms).
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr int kKlTok = 256;     // tokens per workgroup
 
@@ -121,6 +126,7 @@ __global__ __launch_bounds__(512) void lm_kl_kernel(const bf16_t* __restrict__ X
   static_assert(WS % 512 == 0 && (ST - 2) * NL < 16 && ST * SS * 16 <= 160 * 1024, "stage geometry");
   __shared__ __attribute__((aligned(16))) v4u smem[ST * SS];
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, l32 = lane & 31;
+  const int vh = w & 1, tq = w >> 1;
   // Workgroup -> (token block, vocab chunk): the 32 workgroups an XCD runs at once
   // cover 4 token blocks x 8 chunks, so one pass's X rows (4 x 384 KB at d = 768)
   // and the W tiles in use (8 x 192 KB) stay in that XCD's L2 through the passes.
@@ -130,9 +136,13 @@ __global__ __launch_bounds__(512) void lm_kl_kernel(const bf16_t* __restrict__ X
   const int vt0 = (int)((int64_t)chunk * n_vt / n_chunks), vt1 = (int)((int64_t)(chunk + 1) * n_vt / n_chunks);
   const int nk = d / BK;
   const int nsteps = (vt1 - vt0) * (G + 1) * nk;
-  const int token = t0 + w * 32 + l32;
-  float Ac = lse[min(token, rows - 1)] * kLog2e;
-  asm volatile("" : "+v"(Ac));   // loaded before the copies start: no vector-memory wait inside the loop
+  const int token = t0 + tq * 64 + l32;   // and token + 32
+  float Ac[2];
+#pragma unroll
+  for (int tb2 = 0; tb2 < 2; ++tb2) {
+    Ac[tb2] = lse[min(token + tb2 * 32, rows - 1)] * kLog2e;
+    asm volatile("" : "+v"(Ac[tb2]));   // loaded before the copies start: no vector-memory wait inside the loop
+  }
 
   // Copy geometry: in round j a wave instruction fills rows 8 RPI j + RPI w ..
   // + RPI - 1 of a tile, lane -> (row 8 RPI j + RPI w + lane / CH, swizzled chunk);
@@ -173,10 +183,10 @@ __global__ __launch_bounds__(512) void lm_kl_kernel(const bf16_t* __restrict__ X
       advance();
     }
 
-  float T1[GMAX], S[GMAX];
+  float T1[2][GMAX], S[2][GMAX];
 #pragma unroll
-  for (int g = 0; g < GMAX; ++g) { T1[g] = 0.f; S[g] = 0.f; }
-  f32x16_t a[4], b[4];
+  for (int g = 0; g < GMAX; ++g) { T1[0][g] = T1[1][g] = 0.f; S[0][g] = S[1][g] = 0.f; }
+  f32x16_t a[4], b[4];   // block 2 x + y: vocabulary block x, token block y
   int kt = 0, g = -1, slot = 0, pslot = ST - 1;
   constexpr int PER = (NL + NKS - 1) / NKS;   // copies issued per k-slice
   // One k-step of the stream from LDS slot `slot`; COPY: it also issues its share
@@ -196,18 +206,22 @@ __global__ __launch_bounds__(512) void lm_kl_kernel(const bf16_t* __restrict__ X
     }
     const v4u* Wt = smem + slot * SS;
     const v4u* Xt = Wt + WS;
-    bf16x8_t wf[2][4], xf[2];
+    bf16x8_t wf[2][2], xf[2][2];
 #pragma unroll
-    for (int vb = 0; vb < 4; ++vb) wf[0][vb] = frag<CH>(Wt, vb * 32 + l32, 0, lane);
-    xf[0] = frag<CH>(Xt, w * 32 + l32, 0, lane);
+    for (int q = 0; q < 2; ++q) {
+      wf[0][q] = frag<CH>(Wt, vh * 64 + q * 32 + l32, 0, lane);
+      xf[0][q] = frag<CH>(Xt, tq * 64 + q * 32 + l32, 0, lane);
+    }
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int ks = 0; ks < NKS; ++ks) {
       const int c = ks & 1;
       if (ks + 1 < NKS) {
 #pragma unroll
-        for (int vb = 0; vb < 4; ++vb) wf[c ^ 1][vb] = frag<CH>(Wt, vb * 32 + l32, ks + 1, lane);
-        xf[c ^ 1] = frag<CH>(Xt, w * 32 + l32, ks + 1, lane);
+        for (int q = 0; q < 2; ++q) {
+          wf[c ^ 1][q] = frag<CH>(Wt, vh * 64 + q * 32 + l32, ks + 1, lane);
+          xf[c ^ 1][q] = frag<CH>(Xt, tq * 64 + q * 32 + l32, ks + 1, lane);
+        }
       }
       if constexpr (CP) {
 #pragma unroll
@@ -217,7 +231,7 @@ __global__ __launch_bounds__(512) void lm_kl_kernel(const bf16_t* __restrict__ X
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
       for (int vb = 0; vb < 4; ++vb)
-        b[vb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[c][vb], xf[c], b[vb], 0, 0, 0);
+        b[vb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[c][vb >> 1], xf[c][vb & 1], b[vb], 0, 0, 0);
       __builtin_amdgcn_sched_barrier(0);
     }
     if constexpr (CP) {
@@ -234,21 +248,24 @@ __global__ __launch_bounds__(512) void lm_kl_kernel(const bf16_t* __restrict__ X
 #pragma unroll
       for (int vb = 0; vb < 4; ++vb) a[vb] = b[vb];
     } else {
-      float t1 = 0.f, s2 = 0.f;
+      float t1[2] = {0.f, 0.f}, s2[2] = {0.f, 0.f};
 #pragma unroll
       for (int vb = 0; vb < 4; ++vb)
 #pragma unroll
         for (int i = 0; i < 16; ++i) {
           const float av = a[vb][i];
-          const float p = __builtin_amdgcn_exp2f(fmaf(av, kLog2e, -Ac));
+          const float p = __builtin_amdgcn_exp2f(fmaf(av, kLog2e, -Ac[vb & 1]));
           const float dl = av - b[vb][i];
           const float e = __builtin_amdgcn_exp2f(-dl * kLog2e) - 1.0f;
-          t1 = fmaf(p, dl, t1);
-          s2 = fmaf(p, e, s2);
+          t1[vb & 1] = fmaf(p, dl, t1[vb & 1]);
+          s2[vb & 1] = fmaf(p, e, s2[vb & 1]);
         }
 #pragma unroll
       for (int j = 0; j < GMAX; ++j)
-        if (j == g) { T1[j] += t1; S[j] += s2; }
+        if (j == g) {
+#pragma unroll
+          for (int y = 0; y < 2; ++y) { T1[y][j] += t1[y]; S[y][j] += s2[y]; }
+        }
     }
     if (++g == G) g = -1;
   };
@@ -260,12 +277,25 @@ __global__ __launch_bounds__(512) void lm_kl_kernel(const bf16_t* __restrict__ X
     kstep(std::false_type{});
     tile_done();
   }
+  // the half-waves hold other vocabulary rows of the same tokens, the waves vh = 0 and 1
+  // the two halves of the tile: added in that order through LDS
+  __syncthreads();
+  float2* red = reinterpret_cast<float2*>(smem);
 #pragma unroll
-  for (int g2 = 0; g2 < GMAX; ++g2) {
+  for (int g2 = 0; g2 < GMAX; ++g2)
     if (g2 < G) {
-      const float x = T1[g2] + __shfl_xor(T1[g2], 32, 64);
-      const float y = S[g2] + __shfl_xor(S[g2], 32, 64);
-      if ((lane >> 5) == 0 && token < rows) part[((int64_t)chunk * G + g2) * rows + token] = make_float2(x, y);
+#pragma unroll
+      for (int y = 0; y < 2; ++y) {
+        const float tx = T1[y][g2] + __shfl_xor(T1[y][g2], 32, 64), sx = S[y][g2] + __shfl_xor(S[y][g2], 32, 64);
+        if (lane < 32) red[(g2 * 2 + vh) * kKlTok + tq * 64 + y * 32 + l32] = make_float2(tx, sx);
+      }
+    }
+  __syncthreads();
+  for (int q = tid; q < G * kKlTok; q += 512) {
+    const int g2 = q / kKlTok, tk = q % kKlTok;
+    if (t0 + tk < rows) {
+      const float2 x = red[(g2 * 2) * kKlTok + tk], y = red[(g2 * 2 + 1) * kKlTok + tk];
+      part[((int64_t)chunk * G + g2) * rows + t0 + tk] = make_float2(x.x + y.x, x.y + y.y);
     }
   }
 }
