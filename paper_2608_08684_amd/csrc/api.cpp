@@ -621,6 +621,29 @@ static KvPrefix cache_prefix(const rk_model* m, const Win& wn, const SeqTable& p
   return pk;
 }
 
+// The cached prefix of layer l restricted to `keep` retained positions per KV head (pos:
+// of layer l, per sequence at seq_stride), for the rows of st: read in place where the
+// attention takes positions, else gathered into b.cpre.
+static rk_status compressed_prefix(const rk_model* m, const Win& wn, const SeqTable& pst, const SeqTable& st, int l,
+                                   const int32_t* pos, int64_t seq_stride, int keep, const Bufs& b, hipStream_t s,
+                                   KvPrefix* pk) {
+  const rk_model_config& c = m->cfg;
+  const int64_t kc = kv_cols(m);
+  *pk = cache_prefix(m, wn, pst, l, nullptr);
+  if (attention_takes_positions(st, c.n_heads, c.n_kv_heads, c.head_dim, keep, pst.max_len, kc)) {
+    pk->pos = pos;
+    pk->pos_stride = seq_stride;
+    pk->full_P = pst.max_len;
+  } else {
+    RK_TRY(launch_prefix_gather(pk->k, kc, pst.n, pst.max_len, c.n_kv_heads, c.head_dim, pos, seq_stride, keep, b.cpre,
+                                s));
+    pk->k = (const bf16_t*)b.cpre;
+    pk->v = (const bf16_t*)b.cpre + kc / 2;
+  }
+  pk->P = keep;
+  return RK_OK;
+}
+
 // ReferencePredict of the cached-window mode: the prefixes run through every
 // layer once and leave their K and V; the windows are then evaluated against the
 // intact cache, keeping each block's input, the final hidden state and A_t.
@@ -711,18 +734,13 @@ static rk_status batch_attention(const rk_model* m, int l, const Bufs& b, const 
     if (wb.layer[q] == l) { ++n_at_l; alt = q; }
   if (wb.pol) {
     // every pass reads its own (compressed or whole) prompt cache of this layer
-    const char* kv_l = (const char*)wb.wn->kv + (size_t)l * Rp * kc * a;
     for (int q = 0; q < wb.n; ++q) {
       const int keep = wb.pol->keep[q][l];
       KvPrefix pk{};
       if (keep > 0) {
-        RK_TRY(launch_prefix_gather(kv_l, kc, wb.pst->n, wb.pst->max_len, c.n_kv_heads, c.head_dim,
-                                    wb.pol->pos[q] + wb.pol->off[q][l], wb.pol->stride[q], keep, b.cpre, s));
-        pk.alt_pass = -1;
-        pk.k = (const bf16_t*)b.cpre;
-        pk.v = (const bf16_t*)b.cpre + kc / 2;
-        pk.ldk = pk.ldv = kc;
-        pk.P = keep;
+        rk_status e = compressed_prefix(m, *wb.wn, *wb.pst, *wb.wst, l, wb.pol->pos[q] + wb.pol->off[q][l],
+                                        wb.pol->stride[q], keep, b, s, &pk);
+        if (e != RK_OK) return e;
       } else {
         pk = cache_prefix(m, *wb.wn, *wb.pst, l, nullptr);
       }
@@ -747,16 +765,10 @@ static rk_status batch_attention(const rk_model* m, int l, const Bufs& b, const 
       RK_TRY(launch_attention(b.qkv, m->qkv_cols, b.att, m->attn_cols, ft, c.n_heads, c.n_kv_heads, c.head_dim,
                               m->bf16, s, &pk));
     }
-    const char* kv_l = (const char*)wb.wn->kv + (size_t)l * Rp * kc * a;
     for (int q = full; q < wb.n; ++q) {
-      RK_TRY(launch_prefix_gather(kv_l, kc, wb.pst->n, wb.pst->max_len, c.n_kv_heads, c.head_dim, wb.pos[q],
-                                  wb.seq_stride, wb.n_keep, b.cpre, s));
       KvPrefix pk{};
-      pk.alt_pass = -1;
-      pk.k = (const bf16_t*)b.cpre;
-      pk.v = (const bf16_t*)b.cpre + kc / 2;
-      pk.ldk = pk.ldv = kc;
-      pk.P = wb.n_keep;
+      rk_status e = compressed_prefix(m, *wb.wn, *wb.pst, *wb.wst, l, wb.pos[q], wb.seq_stride, wb.n_keep, b, s, &pk);
+      if (e != RK_OK) return e;
       Timed t("attention", s);
       RK_TRY(launch_attention((const char*)b.qkv + (size_t)q * wb.rw * m->qkv_cols * a, m->qkv_cols,
                               (char*)b.att + (size_t)q * wb.rw * m->attn_cols * a, m->attn_cols, *wb.wst, c.n_heads,
@@ -902,16 +914,10 @@ static rk_status window_compressed_final(const rk_model* m, const SeqTable& pst,
                                          const Bufs& bf, hipStream_t s) {
   const rk_model_config& c = m->cfg;
   const int64_t d = c.d_model, Rp = pst.rows, Rw = wst.rows, a = act_bytes(m), kc = kv_cols(m);
-  const char* kv_l = (const char*)wn.kv + (size_t)layer * Rp * kc * a;
-  RK_TRY(launch_prefix_gather(kv_l, kc, pst.n, pst.max_len, c.n_kv_heads, c.head_dim, pos, seq_stride, b, bf.cpre,
-                              s));
   KvPrefix pk{};
-  pk.alt_pass = -1;
-  pk.k = (const bf16_t*)bf.cpre;
-  pk.v = (const bf16_t*)bf.cpre + kc / 2;
-  pk.ldk = pk.ldv = kc;
-  pk.P = b;
-  rk_status e = run_block(m, layer, wn.w.h + (size_t)layer * Rw * d, bf.h, bf, wst, nullptr, s, &pk);
+  rk_status e = compressed_prefix(m, wn, pst, wst, layer, pos, seq_stride, b, bf, s, &pk);
+  if (e != RK_OK) return e;
+  e = run_block(m, layer, wn.w.h + (size_t)layer * Rw * d, bf.h, bf, wst, nullptr, s, &pk);
   if (e != RK_OK) return e;
   for (int l = layer + 1; l < c.n_layers; ++l) {
     pk = cache_prefix(m, wn, pst, l, nullptr);
@@ -937,14 +943,8 @@ static rk_status window_policy_final(const rk_model* m, const SeqTable& pst, con
   for (int l = 0; l < c.n_layers; ++l) {
     KvPrefix pk{};
     if (n_keep[l] > 0) {
-      const char* kv_l = (const char*)wn.kv + (size_t)l * Rp * kc * a;
-      RK_TRY(launch_prefix_gather(kv_l, kc, pst.n, pst.max_len, c.n_kv_heads, c.head_dim, positions + layer_off[l],
-                                  seq_stride, n_keep[l], bf.cpre, s));
-      pk.alt_pass = -1;
-      pk.k = (const bf16_t*)bf.cpre;
-      pk.v = (const bf16_t*)bf.cpre + kc / 2;
-      pk.ldk = pk.ldv = kc;
-      pk.P = n_keep[l];
+      rk_status e = compressed_prefix(m, wn, pst, wst, l, positions + layer_off[l], seq_stride, n_keep[l], bf, s, &pk);
+      if (e != RK_OK) return e;
     } else {
       pk = cache_prefix(m, wn, pst, l, nullptr);
     }

@@ -73,6 +73,13 @@ __device__ __forceinline__ void wait_vm() {
   __builtin_amdgcn_s_waitcnt(0x0F70 | N);
 }
 
+// s_waitcnt vmcnt(N), N < 64
+template <int N>
+__device__ __forceinline__ void wait_vmem_few() {
+  static_assert(N >= 0 && N < 64, "vmcnt field");
+  __builtin_amdgcn_s_waitcnt(0x0F70 | (N & 15) | ((N >> 4) << 14));
+}
+
 // 16-byte chunk swizzles that keep the LDS reads free of bank conflicts (64
 // banks of 4 bytes): the K tile is read as 16 rows x one chunk per quarter-wave,
 // the V tile by ds_read_b64_tr_b16 as 4 rows x 4 chunks per half-wave.
@@ -372,6 +379,216 @@ __global__ __launch_bounds__(64 * AttnTraits<DH>::kWaves, AttnTraits<DH>::kMinBl
   }
 }
 
+// Few query rows behind a cached prefix (a decode step, short windows): the rows of
+// all query heads of one KV head together are at most 32 columns, so one workgroup =
+// 4 waves serves a (sequence, KV head).  The waves share out the 32-key blocks (wave w
+// takes blocks w, w + 4, ...: the prefix's, then the rows' own), each through a two-stage
+// ring of its own (it alone writes and reads it, so it waits on its own copies and
+// needs no barrier), with its own running maximum, denominator and output; merged through
+// LDS in wave order.  A prefix restricted to retained positions is read in place: the
+// positions lie in LDS and give each copied row its offset.
+// Bound: latency of the copies and of a block's chain; 128 KB of copies in flight per CU.
+// With one workgroup of 8 waves per query head, of whose 256 query columns one was
+// used, 16 sequences, 32 / 8 heads of 128, 300 to 510 keys: 49 us and 12 us for gathering
+// them; now 10 to 17 in all.
+constexpr int kFewRows = 32, kFewPos = 4096;
+
+template <int DH>
+__global__ __launch_bounds__(256) void attn_few_kernel(const bf16_t* __restrict__ qkv, int64_t ldq,
+                                                       bf16_t* __restrict__ out, int64_t ldo, SeqTable st, int H,
+                                                       int Hkv, KvPrefix pk) {
+  constexpr int CH = DH / 8, NKS = DH / 16, NDB = DH / 32, ROWB = DH * 2, SP = DH + 4;
+  constexpr int SLOTS = 32 * CH, NI = SLOTS / 64, RPI = 64 / CH;   // copies per block and matrix, rows per copy
+  // per wave: two stages of K and V blocks; the outputs of the waves at the end
+  __shared__ __attribute__((aligned(16))) v4u ring[4][2][2][SLOTS];
+  __shared__ float sm[4][32], sl[4][32];
+  __shared__ int32_t spos[kFewPos];
+  static_assert(4 * 32 * SP * 4 <= (int)sizeof(ring), "merge area");
+  const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, hf = lane >> 5;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int k = blockIdx.x / Hkv, hk = blockIdx.x - k * Hkv, grp = H / Hkv;
+  const int row0 = st.off[k], T = st.off[k + 1] - row0;
+  if (T <= 0) return;   // the whole workgroup
+  const int ps = pk.n_seq > 0 ? k % pk.n_seq : k;
+  const bool alt = pk.n_seq > 0 && k / pk.n_seq == pk.alt_pass;
+  const int P = pk.P, PR = pk.pos ? pk.full_P : P;   // keys, cached rows per sequence
+  if (pk.pos) {
+    const int32_t* pp = pk.pos + (int64_t)ps * pk.pos_stride + (int64_t)hk * P;
+    for (int j = tid; j < P; j += 256) spos[j] = min(max(pp[j], 0), PR - 1);
+    __syncthreads();
+  }
+  const int64_t ldv = alt ? pk.ldv_alt : pk.ldv;
+  auto make_rsrc = [](const bf16_t* base_ptr, int64_t bytes) {
+    i32x4_t r;
+    const uint64_t base = (uint64_t)base_ptr;
+    r[0] = __builtin_amdgcn_readfirstlane((int32_t)(uint32_t)base);
+    r[1] = __builtin_amdgcn_readfirstlane((int32_t)(uint32_t)(base >> 32));
+    r[2] = __builtin_amdgcn_readfirstlane((int32_t)bytes);
+    r[3] = 0x00020000;
+    return r;
+  };
+  const i32x4_t rk_p = make_rsrc(pk.k + (int64_t)ps * PR * pk.ldk, (int64_t)PR * pk.ldk * 2);
+  const i32x4_t rv_p = make_rsrc((alt ? pk.v_alt : pk.v) + (int64_t)ps * PR * ldv, (int64_t)PR * ldv * 2);
+  const i32x4_t rsrc = make_rsrc(qkv + (int64_t)row0 * ldq, (int64_t)T * ldq * 2);
+  const uint32_t lds_k = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) v4u*)&ring[w][0][0][0];
+  const int n_pre = (P + 31) / 32, n_blk = n_pre + (T + 31) / 32;
+  // block b into stage st_: rows past the prefix or the sequence read as zero (a prefix
+  // block's rows past P are other rows or zero: masked)
+  auto issue = [&](int b, int stage) {
+    const bool pre = b < n_pre;
+    const int k0 = (pre ? b : b - n_pre) * 32;
+    const uint32_t ldk2 = (uint32_t)((pre ? pk.ldk : ldq) * 2), ldv2 = (uint32_t)((pre ? ldv : ldq) * 2);
+    const uint32_t kc = (uint32_t)((pre ? hk : H + hk) * ROWB), vc = (uint32_t)((pre ? hk : H + Hkv + hk) * ROWB);
+    const uint32_t base = lds_k + (uint32_t)(stage * 2 * SLOTS * 16);
+#pragma unroll
+    for (int i = 0; i < NI; ++i) {
+      const int r = i * RPI + lane / CH, ph = lane % CH;
+      int row = k0 + r;
+      if (pre && pk.pos) row = spos[min(row, P - 1)];
+      const uint32_t ko = (uint32_t)row * ldk2 + kc + (uint32_t)((ph ^ k_swz<DH>(r)) * 16);
+      const uint32_t vo = (uint32_t)row * ldv2 + vc + (uint32_t)((ph ^ v_swz<DH>(r)) * 16);
+      const uint32_t lk = __builtin_amdgcn_readfirstlane(base + i * 1024);
+      if (pre) {
+        dma16(rk_p, lk, ko, 0);
+        dma16(rv_p, lk + SLOTS * 16, vo, 0);
+      } else {
+        dma16(rsrc, lk, ko, 0);
+        dma16(rsrc, lk + SLOTS * 16, vo, 0);
+      }
+    }
+  };
+  // column c = l32: query head c / T of the group, row c % T (columns past grp * T repeat the last)
+  const int c = min(l32, grp * T - 1), my_t = c % T, hq = hk * grp + c / T;
+  bf16x8_t qf[NKS];
+  {
+    const bf16_t* qp = qkv + (int64_t)(row0 + my_t) * ldq + (int64_t)hq * DH + hf * 8;
+#pragma unroll
+    for (int ks = 0; ks < NKS; ++ks) qf[ks] = __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const v4u*>(qp + ks * 16));
+  }
+  int kfo[NKS], vfo[NDB];
+#pragma unroll
+  for (int ks = 0; ks < NKS; ++ks) kfo[ks] = l32 * ROWB + (((2 * ks + hf) ^ k_swz<DH>(l32)) << 4);
+  {
+    const int G = lane >> 4, jj = lane & 15, r = 4 * (G >> 1) + (jj >> 2);
+#pragma unroll
+    for (int db = 0; db < NDB; ++db) {
+      const int chv = 4 * db + 2 * (G & 1) + ((jj & 3) >> 1);
+      vfo[db] = r * ROWB + ((chv ^ v_swz<DH>(r)) << 4) + (jj & 1) * 8;
+    }
+  }
+  const bf16x2_t ones = {(__bf16)1.0f, (__bf16)1.0f};
+  f32x16_t o[NDB];
+#pragma unroll
+  for (int db = 0; db < NDB; ++db)
+#pragma unroll
+    for (int i = 0; i < 16; ++i) o[db][i] = 0.f;
+  float m = -INFINITY, l = 0.f;
+  wait_vm0();   // the query fragments are in registers before the ring starts
+  if (w < n_blk) issue(w, 0);
+  int stage = 0;
+  for (int b = w; b < n_blk; b += 4) {
+    if (b + 4 < n_blk) {
+      issue(b + 4, stage ^ 1);
+      wait_vmem_few<2 * NI>();
+    } else {
+      wait_vm0();
+    }
+    asm volatile("" ::: "memory");
+    const bool pre = b < n_pre;
+    const int k0 = (pre ? b : b - n_pre) * 32;
+    const char* kt = reinterpret_cast<const char*>(&ring[w][stage][0][0]);
+    const char* vt = reinterpret_cast<const char*>(&ring[w][stage][1][0]);
+    f32x16_t s;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) s[i] = 0.f;
+#pragma unroll
+    for (int ks = 0; ks < NKS; ++ks)
+      s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+          __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const v4u*>(kt + kfo[ks])), qf[ks], s, 0, 0, 0);
+    const int lim = pre ? P - 1 : my_t;   // last visible key of the segment
+    if (pre ? k0 + 32 > P : true) {
+#pragma unroll
+      for (int i = 0; i < 16; ++i)
+        if (k0 + (i >> 2) * 8 + hf * 4 + (i & 3) > lim) s[i] = -INFINITY;
+    }
+    float mx = s[0];
+#pragma unroll
+    for (int i = 1; i < 16; ++i) mx = fmaxf(mx, s[i]);
+    const float m_new = fmaxf(m, max_halves(mx));
+    const float ref = m_new == -INFINITY ? 0.f : m_new;   // an own block past the query's row
+    const float corr = __builtin_amdgcn_exp2f(m - ref);   // 0 on the first block (m = -inf)
+    m = m_new;
+    l *= corr;
+#pragma unroll
+    for (int db = 0; db < NDB; ++db)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) o[db][i] *= corr;
+#pragma unroll
+    for (int ss = 0; ss < 2; ++ss) {
+      bf16x8_t pb;
+#pragma unroll
+      for (int e = 0; e < 8; ++e) pb[e] = (__bf16)__builtin_amdgcn_exp2f(s[8 * ss + e] - ref);
+#pragma unroll
+      for (int e = 0; e < 8; e += 2) {
+        const bf16x2_t pr = {pb[e], pb[e + 1]};
+        l = __builtin_amdgcn_fdot2_f32_bf16(pr, ones, l, false);
+      }
+      const int kr = ss * 16 * ROWB;
+#pragma unroll
+      for (int db = 0; db < NDB; ++db) {
+        const s16x4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(vt + kr + vfo[db]));
+        const s16x4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(vt + kr + 8 * ROWB + vfo[db]));
+        const v4u vv = {__builtin_bit_cast(v2u, lo)[0], __builtin_bit_cast(v2u, lo)[1], __builtin_bit_cast(v2u, hi)[0],
+                        __builtin_bit_cast(v2u, hi)[1]};
+        o[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, vv), pb, o[db], 0, 0, 0);
+      }
+    }
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // this stage is copied into next
+    stage ^= 1;
+  }
+  l = sum_halves(l);
+  if (hf == 0) {
+    sm[w][l32] = m;
+    sl[w][l32] = l;
+  }
+  __syncthreads();   // every ring is drained: its area holds the outputs now
+  float* so = reinterpret_cast<float*>(&ring[0][0][0][0]);
+#pragma unroll
+  for (int db = 0; db < NDB; ++db)
+#pragma unroll
+    for (int g = 0; g < 4; ++g)
+      *reinterpret_cast<f32x4_t*>(so + (w * 32 + l32) * SP + db * 32 + g * 8 + hf * 4) =
+          f32x4_t{o[db][4 * g], o[db][4 * g + 1], o[db][4 * g + 2], o[db][4 * g + 3]};
+  __syncthreads();
+  const int q = tid >> 3;
+  if (q >= grp * T) return;
+  float M = sm[0][q];
+#pragma unroll
+  for (int j = 1; j < 4; ++j) M = fmaxf(M, sm[j][q]);   // finite: a row sees its own key
+  float f[4], L = 0.f;
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    f[j] = __builtin_amdgcn_exp2f(sm[j][q] - M);
+    L += sl[j][q] * f[j];
+  }
+  const float inv = 1.0f / L;
+  bf16_t* op = out + (int64_t)(row0 + q % T) * ldo + (int64_t)(hk * grp + q / T) * DH;
+#pragma unroll
+  for (int cc = (tid & 7) * 4; cc < DH; cc += 32) {
+    f32x4_t a = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const f32x4_t x = *reinterpret_cast<const f32x4_t*>(so + (j * 32 + q) * SP + cc);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) a[e] += x[e] * f[j];
+    }
+    bf16x4_t u;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) u[e] = (__bf16)(a[e] * inv);
+    *reinterpret_cast<bf16x4_t*>(op + cc) = u;
+  }
+}
+
 // fp32: one workgroup = 4 waves for 32 queries of one head.  The waves share out the
 // 32-key blocks (wave w takes blocks w, w + 4, ...), each with its own running
 // maximum, denominator and output, merged through LDS in wave order.  S^T = K Q^T and
@@ -519,6 +736,15 @@ static AttnWork attn_work(const SeqTable& st, const F& items) {
   return wk;
 }
 
+static bool few_rows(const SeqTable& st, int n_heads, int n_kv_heads) {
+  return (int64_t)st.max_len * (n_heads / n_kv_heads) <= kFewRows;
+}
+
+bool attention_takes_positions(const SeqTable& st, int n_heads, int n_kv_heads, int head_dim, int keep, int full_P,
+                               int64_t ld) {
+  return few_rows(st, n_heads, n_kv_heads) && keep <= kFewPos && (int64_t)full_P * ld * 2 < ((int64_t)1 << 31);
+}
+
 hipError_t launch_attention(const void* qkv, int64_t ldq, void* out, int64_t ldo, const SeqTable& st, int n_heads,
                             int n_kv_heads, int head_dim, bool bf16, hipStream_t s, const KvPrefix* prefix) {
   if (st.rows <= 0) return hipSuccess;
@@ -545,10 +771,23 @@ hipError_t launch_attention(const void* qkv, int64_t ldq, void* out, int64_t ldo
     KvPrefix pk{};
     if (pre) {
       pk = *prefix;
+      if (pk.pos && !attention_takes_positions(st, n_heads, n_kv_heads, head_dim, pk.P, pk.full_P,
+                                               std::max(pk.ldk, pk.ldv)))
+        return hipErrorInvalidValue;
       // one descriptor per sequence's cached prefix, also with 32-bit byte offsets
       const int64_t ld = std::max(std::max(pk.ldk, pk.ldv), pk.alt_pass >= 0 && pk.n_seq > 0 ? pk.ldv_alt : 0);
       if ((int64_t)pk.P * ld * 2 >= ((int64_t)1 << 31)) return hipErrorInvalidValue;
       if (pk.n_seq > 0 && (st.n % pk.n_seq != 0 || (pk.alt_pass >= 0 && !pk.v_alt))) return hipErrorInvalidValue;
+    }
+    if (pre && few_rows(st, n_heads, n_kv_heads)) {
+      if (head_dim == 128)
+        attn_few_kernel<128><<<st.n * n_kv_heads, 256, 0, s>>>((const bf16_t*)qkv, ldq, (bf16_t*)out, ldo, st, n_heads,
+                                                               n_kv_heads, pk);
+      else if (head_dim == 64)
+        attn_few_kernel<64><<<st.n * n_kv_heads, 256, 0, s>>>((const bf16_t*)qkv, ldq, (bf16_t*)out, ldo, st, n_heads,
+                                                              n_kv_heads, pk);
+      else return hipErrorInvalidValue;
+      return hipGetLastError();
     }
 #define RK_ATTN(D, PRE)                                                                                      \
   attn_bf16_kernel<D, PRE><<<grid, 64 * AttnTraits<D>::kWaves, 0, s>>>((const bf16_t*)qkv, ldq, (bf16_t*)out, ldo, \

@@ -125,7 +125,17 @@ struct KvPrefix {
   int64_t ldv_alt;
   int32_t n_seq;
   int32_t alt_pass;
+  // Retained positions (NULL: rows 0 .. P - 1): cached position j of KV head h of
+  // sequence s is row pos[s * pos_stride + h * P + j] (clamped) of the full_P rows per
+  // sequence of k and v.  Only where attention_takes_positions.
+  const int32_t* pos;
+  int64_t pos_stride;
+  int32_t full_P;
 };
+// Whether the attention of these rows behind a cached prefix reads retained positions
+// (keep per KV head, of full_P rows of ld elements) in place: few query rows.
+bool attention_takes_positions(const SeqTable& st, int n_heads, int n_kv_heads, int head_dim, int keep, int full_P,
+                               int64_t ld);
 
 hipError_t launch_attention(const void* qkv, int64_t ldq, void* out, int64_t ldo, const SeqTable& st,
                             int n_heads, int n_kv_heads, int head_dim, bool bf16, hipStream_t s,
