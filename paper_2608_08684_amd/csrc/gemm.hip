@@ -531,16 +531,18 @@ __global__ __launch_bounds__(64 * NW) void gemm_ring_kernel(const T* __restrict_
                                                             int64_t lda, const T* __restrict__ B, int64_t ldb, int M,
                                                             int K, int d_ff, int n_bn, E e) {
   constexpr bool F32 = sizeof(T) == 4;
-  constexpr int GW = (BM / 32) * (BN / 32), NT = 64 * NW, HB = BN / 2, CH = 8;
+  constexpr int WN = BN < 32 ? 1 : BN / 32;          // 32-column blocks (a 16-wide tile fills half of one)
+  constexpr int GW = (BM / 32) * WN, NT = 64 * NW, HB = BN / 2, CH = 8;
   constexpr int SA = BM * CH, SS = (BM + BN) * CH;   // 16-byte slots of a stage's A tile, of a stage
+  constexpr int PAD = (WN * 32 - BN) * CH;           // read past a 16-wide tile's last stage, never used
   constexpr int NG = (BM + BN) / 8, NL = NG / NW;    // 8-row groups of a stage, copies per wave
   static_assert(NW >= GW && NG % NW == 0 && S >= 3 && (S - 2) * NL < 64, "copies split evenly");
   constexpr int SP = BN + 4;                         // staged row in floats
-  static_assert(S * SS * 16 <= 160 * 1024 && BM * SP * 4 <= S * SS * 16, "LDS");
-  __shared__ __attribute__((aligned(16))) v4u smem[S * SS];
+  static_assert((S * SS + PAD) * 16 <= 160 * 1024 && BM * SP * 4 <= S * SS * 16, "LDS");
+  __shared__ __attribute__((aligned(16))) v4u smem[S * SS + PAD];
   const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int wm = w / (BN / 32), wn = w % (BN / 32);
+  const int wm = w / WN, wn = w % WN;
   int bm_, bn;
   const int n_bm = (M + BM - 1) / BM, n_m = A2 ? 2 * n_bm : n_bm;
   xcd_tile((int)blockIdx.x, n_m, n_bn, n_m, &bm_, &bn);   // the row tiles of one column block together
@@ -669,7 +671,8 @@ __global__ __launch_bounds__(64 * NW) void gemm_ring_kernel(const T* __restrict_
     // acc is the transposed block: lane l holds row l % 32, columns 8 g + 4 (l / 32) .. + 3
     float* cs = Cs + (wm * 32 + l32) * SP + wn * 32 + (lane >> 5) * 4;
 #pragma unroll
-    for (int g = 0; g < 4; ++g) store4(cs + g * 8, make_float4(acc[4 * g], acc[4 * g + 1], acc[4 * g + 2], acc[4 * g + 3]));
+    for (int g = 0; g < (BN < 32 ? BN / 8 : 4); ++g)
+      store4(cs + g * 8, make_float4(acc[4 * g], acc[4 * g + 1], acc[4 * g + 2], acc[4 * g + 3]));
   }
   __syncthreads();
   constexpr int QPR = HB / 4;   // four-column units per run
@@ -705,7 +708,7 @@ static int cu_count() {
 // 0.108, 0.13 (16 rows, N = 4096, K = 14336: 66, 45, 33, 27 us; 509 rows, N = 768, K = 3072:
 // 16, 11.9, 9.1, 10.6).  No tile beats the time the weights take from memory (5.5 TB/s);
 // among equals the one listed first is taken.
-enum class Tile { k32x64, k32x32, k64x64, k64x128, k256x128, k256x192, k256x256 };
+enum class Tile { k32x16, k32x64, k32x32, k64x64, k64x128, k256x128, k256x192, k256x256 };
 
 static Tile pick_tile(const GemmArgs& a, bool swiglu) {
   const int64_t ncu = cu_count(), nk = a.K / kBK;
@@ -726,6 +729,10 @@ static Tile pick_tile(const GemmArgs& a, bool swiglu) {
     const int64_t n = tiles(bm, bn);
     offer(t, rounds(n, ncu) * (fixed + nk * step * (1.0 + load * (n < ncu ? (double)n / ncu : 1.0))));
   };
+  // 32x16 tiles put twice the CUs on weights that stream from memory; worth it where K is
+  // long enough for their 24-stage ring (16 rows, N = 4096, cold weights: K = 14336 41.6 -> 37
+  // us, K = 4096 12.6 -> 14.2; a decode step of 8 blocks 1.41 -> 1.38 ms)
+  if (nk >= 128 && tiles(32, 16) <= ncu) one(Tile::k32x16, 32, 16, 3.0, 0.1, 0.0);
   two(Tile::k32x64, 32, 64, 0.13, 0.17);
   two(Tile::k32x32, 32, 32, 0.108, 0.13);
   two(Tile::k64x64, 64, 64, 0.195, 0.36);
@@ -781,7 +788,7 @@ static hipError_t go(const GemmArgs& a, bool bf16, const E& e, hipStream_t s) {
     if (E::kPaired && !SWIGLU && a.head_dim != 64 && a.head_dim != 128) return hipErrorInvalidValue;
     const Tile tile = pick_tile(a, SWIGLU);
     // the 8-wave tiles take the second rows (the LM head only) in a launch of their own
-    if (a.A2 && tile != Tile::k32x64 && tile != Tile::k32x32 && tile != Tile::k64x64 && tile != Tile::k64x128) {
+    if (a.A2 && tile != Tile::k32x16 && tile != Tile::k32x64 && tile != Tile::k32x32 && tile != Tile::k64x64 && tile != Tile::k64x128) {
       if constexpr (std::is_same<E, EpiStoreF32>::value) {
         GemmArgs one = a;
         one.A2 = nullptr;
@@ -793,6 +800,7 @@ static hipError_t go(const GemmArgs& a, bool bf16, const E& e, hipStream_t s) {
       return hipErrorInvalidValue;
     }
     switch (tile) {
+      case Tile::k32x16: return go_ring<bf16_t, 32, 16, 6, 24>(a, e, s);
       case Tile::k32x64: return go_ring<bf16_t, 32, 64, 4, 6>(a, e, s);
       case Tile::k32x32: return go_ring<bf16_t, 32, 32, 4, 9>(a, e, s);
       case Tile::k64x64: return go_ring<bf16_t, 64, 64, 4, 5>(a, e, s);

@@ -123,7 +123,9 @@ def test_large_tiles(m, lengths):
     (Shape(1024, 8, 2, 128, 1088), [300, 1, 99]),
     (Shape(768, 12, 12, 64, 3072), [700, 1300]),
     (Shape(2048, 16, 8, 128, 640), [900, 101]),
-], ids=["1row", "34", "k320", "k576", "509", "400", "2000", "wide"])
+    (Shape(128, 2, 1, 64, 8192), [17]),                    # long K, 16-wide tiles
+    (Shape(512, 8, 2, 64, 8256), [32, 1]),
+], ids=["1row", "34", "k320", "k576", "509", "400", "2000", "wide", "k8192", "k8256"])
 def test_few_rows(m, lengths):
     check_block(m, lengths)
 
