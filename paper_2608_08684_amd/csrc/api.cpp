@@ -349,13 +349,14 @@ static rk_status run_block(const rk_model* m, int l, const float* h_in, float* h
       const size_t slot = (size_t)noise->one->rows * m->qkv_cols * act_bytes(m);
       for (int k = 0; k < noise->n; ++k) {
         Timed t("noise", s);
-        RK_TRY(launch_value_noise(v + (size_t)(noise->first + k) * slot, m->bf16, m->qkv_cols, *noise->one,
-                                  c.n_kv_heads, c.head_dim, l, noise->alphas[k], noise->p->seed,
+        char* vk = v + (size_t)(noise->first + k) * slot;
+        RK_TRY(launch_value_noise(vk, m->qkv_cols, vk, m->bf16, m->qkv_cols, *noise->one, c.n_kv_heads,
+                                  c.head_dim, l, noise->alphas[k], noise->p->seed,
                                   noise->p->protect_head, noise->p->protect_tail, s));
       }
     } else {
       Timed t("noise", s);
-      RK_TRY(launch_value_noise(v, m->bf16, m->qkv_cols, st, c.n_kv_heads, c.head_dim, l, noise->alpha,
+      RK_TRY(launch_value_noise(v, m->qkv_cols, v, m->bf16, m->qkv_cols, st, c.n_kv_heads, c.head_dim, l, noise->alpha,
                                 noise->p->seed, noise->p->protect_head, noise->p->protect_tail, s));
     }
   }
@@ -686,11 +687,10 @@ static rk_status window_perturbed_block(const rk_model* m, const SeqTable& pst, 
   const rk_model_config& c = m->cfg;
   const int64_t d = c.d_model, Rp = pst.rows, Rw = wst.rows, a = act_bytes(m), kc = kv_cols(m);
   const char* kv_l = (const char*)wn.kv + (size_t)layer * Rp * kc * a;
-  RK_TRY(launch_copy_cols(kv_l, kc * a, (kc / 2) * a, b.vpert, (kc / 2) * a, (kc / 2) * a, (int)Rp, s));
   {
     Timed t("noise", s);
-    RK_TRY(launch_value_noise(b.vpert, m->bf16, kc / 2, pst, c.n_kv_heads, c.head_dim, layer, alpha, p->seed,
-                              p->protect_head, p->protect_tail, s));
+    RK_TRY(launch_value_noise(kv_l + (kc / 2) * a, kc, b.vpert, m->bf16, kc / 2, pst, c.n_kv_heads, c.head_dim,
+                              layer, alpha, p->seed, p->protect_head, p->protect_tail, s));
   }
   const KvPrefix pk = cache_prefix(m, wn, pst, layer, b.vpert);
   return run_block(m, layer, wn.w.h + (size_t)layer * Rw * d, b.h, b, wst, nullptr, s, &pk);
@@ -782,10 +782,9 @@ static rk_status batch_attention(const rk_model* m, int l, const Bufs& b, const 
     pk.n_seq = wb.wst->n;
     if (alt >= 0) {
       const char* kv_l = (const char*)wb.wn->kv + (size_t)l * Rp * kc * a;
-      RK_TRY(launch_copy_cols(kv_l, kc * a, (kc / 2) * a, b.vpert, (kc / 2) * a, (kc / 2) * a, (int)Rp, s));
       Timed t("noise", s);
-      RK_TRY(launch_value_noise(b.vpert, m->bf16, kc / 2, *wb.pst, c.n_kv_heads, c.head_dim, l, wb.alpha[alt],
-                                wb.p->seed, wb.p->protect_head, wb.p->protect_tail, s));
+      RK_TRY(launch_value_noise(kv_l + (kc / 2) * a, kc, b.vpert, m->bf16, kc / 2, *wb.pst, c.n_kv_heads,
+                                c.head_dim, l, wb.alpha[alt], wb.p->seed, wb.p->protect_head, wb.p->protect_tail, s));
       pk.alt_pass = alt;
       pk.v_alt = (const bf16_t*)b.vpert;
       pk.ldv_alt = kc / 2;
@@ -799,10 +798,9 @@ static rk_status batch_attention(const rk_model* m, int l, const Bufs& b, const 
     const void* vp = nullptr;
     if (wb.layer[q] == l) {   // this pass's layer: a perturbed copy of the cached prefix Values
       const char* kv_l = (const char*)wb.wn->kv + (size_t)l * Rp * kc * a;
-      RK_TRY(launch_copy_cols(kv_l, kc * a, (kc / 2) * a, b.vpert, (kc / 2) * a, (kc / 2) * a, (int)Rp, s));
       Timed t("noise", s);
-      RK_TRY(launch_value_noise(b.vpert, m->bf16, kc / 2, *wb.pst, c.n_kv_heads, c.head_dim, l, wb.alpha[q],
-                                wb.p->seed, wb.p->protect_head, wb.p->protect_tail, s));
+      RK_TRY(launch_value_noise(kv_l + (kc / 2) * a, kc, b.vpert, m->bf16, kc / 2, *wb.pst, c.n_kv_heads,
+                                c.head_dim, l, wb.alpha[q], wb.p->seed, wb.p->protect_head, wb.p->protect_tail, s));
       vp = b.vpert;
     }
     const KvPrefix pk = cache_prefix(m, *wb.wn, *wb.pst, l, vp);
@@ -1988,7 +1986,7 @@ rk_status rk_perturb_values(const rk_model* m, const rk_batch* batch, int32_t la
   if ((e = make_table(m, batch, 0, batch->n_seqs, &st)) != RK_OK) return e;
   const rk_model_config& c = m->cfg;
   if (c.head_dim != 32 && c.head_dim != 64 && c.head_dim != 128) { set_error("head_dim unsupported"); return RK_ERR_UNSUPPORTED; }
-  RK_TRY(launch_value_noise(v, m->bf16, row_stride, st, c.n_kv_heads, c.head_dim, layer, alpha, p->seed,
+  RK_TRY(launch_value_noise(v, row_stride, v, m->bf16, row_stride, st, c.n_kv_heads, c.head_dim, layer, alpha, p->seed,
                             p->protect_head, p->protect_tail, (hipStream_t)stream));
   return RK_OK;
 }

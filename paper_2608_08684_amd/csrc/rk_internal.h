@@ -83,7 +83,9 @@ hipError_t launch_embed_gather(const void* emb, bool emb_bf16, const int32_t* to
                                const SeqTable& dst, int pos0, float* h, int d, hipStream_t s);
 hipError_t launch_copy_cols(const void* src, int64_t ld_src_bytes, int64_t off_bytes, void* dst, int64_t ld_dst_bytes,
                             int64_t nbytes, int rows, hipStream_t s);
-hipError_t launch_value_noise(void* v, bool bf16, int64_t row_stride, const SeqTable& st, int n_kv_heads,
+// The perturbed Values of src (rows of src_stride elements) into v (src may be v).
+hipError_t launch_value_noise(const void* src, int64_t src_stride, void* v, bool bf16, int64_t row_stride,
+                              const SeqTable& st, int n_kv_heads,
                               int head_dim, int layer, float alpha, uint64_t seed, int protect_head,
                               int protect_tail, hipStream_t s);
 
