@@ -631,7 +631,7 @@ static rk_status compressed_prefix(const rk_model* m, const Win& wn, const SeqTa
   const rk_model_config& c = m->cfg;
   const int64_t kc = kv_cols(m);
   *pk = cache_prefix(m, wn, pst, l, nullptr);
-  if (attention_takes_positions(st, c.n_heads, c.n_kv_heads, c.head_dim, keep, pst.max_len, kc)) {
+  if (attention_takes_positions(st, c.n_heads, c.n_kv_heads, keep, pst.max_len, kc)) {
     pk->pos = pos;
     pk->pos_stride = seq_stride;
     pk->full_P = pst.max_len;

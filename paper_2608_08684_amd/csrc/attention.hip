@@ -408,7 +408,7 @@ __global__ __launch_bounds__(256) void attn_few_kernel(const bf16_t* __restrict_
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int k = blockIdx.x / Hkv, hk = blockIdx.x - k * Hkv, grp = H / Hkv;
   const int row0 = st.off[k], T = st.off[k + 1] - row0;
-  if (T <= 0) return;   // the whole workgroup
+  if (T <= 0 || (int64_t)T * grp > kFewRows) return;   // the whole workgroup: such a sequence is attn_bf16_kernel's
   const int ps = pk.n_seq > 0 ? k % pk.n_seq : k;
   const bool alt = pk.n_seq > 0 && k / pk.n_seq == pk.alt_pass;
   const int P = pk.P, PR = pk.pos ? pk.full_P : P;   // keys, cached rows per sequence
@@ -736,13 +736,17 @@ static AttnWork attn_work(const SeqTable& st, const F& items) {
   return wk;
 }
 
-static bool few_rows(const SeqTable& st, int n_heads, int n_kv_heads) {
-  return (int64_t)st.max_len * (n_heads / n_kv_heads) <= kFewRows;
+// Whether a sequence of len rows behind a cached prefix takes attn_few_kernel.  By its own
+// length: the two kernels round differently, and a sequence's result is the same beside
+// any others.
+static bool few_rows(int len, int n_heads, int n_kv_heads) {
+  return (int64_t)len * (n_heads / n_kv_heads) <= kFewRows;
 }
 
-bool attention_takes_positions(const SeqTable& st, int n_heads, int n_kv_heads, int head_dim, int keep, int full_P,
-                               int64_t ld) {
-  return few_rows(st, n_heads, n_kv_heads) && keep <= kFewPos && (int64_t)full_P * ld * 2 < ((int64_t)1 << 31);
+// Only attn_few_kernel takes positions; beside longer sequences all read gathered caches,
+// with the same result.
+bool attention_takes_positions(const SeqTable& st, int n_heads, int n_kv_heads, int keep, int full_P, int64_t ld) {
+  return few_rows(st.max_len, n_heads, n_kv_heads) && keep <= kFewPos && (int64_t)full_P * ld * 2 < ((int64_t)1 << 31);
 }
 
 hipError_t launch_attention(const void* qkv, int64_t ldq, void* out, int64_t ldo, const SeqTable& st, int n_heads,
@@ -756,13 +760,19 @@ hipError_t launch_attention(const void* qkv, int64_t ldq, void* out, int64_t ldo
     // adds to the longest item's time (509 rows, 12 heads of 64: 24 pairs of up to 10 tiles
     // 14.1 us, 48 blocks of up to 8 tiles 10.8).
     int64_t blocks = 0;
-    for (int k = 0; k < st.n; ++k) blocks += (st.off[k + 1] - st.off[k] + bq - 1) / bq;
+    int n_few = 0;   // sequences of attn_few_kernel: no items here
+    for (int k = 0; k < st.n; ++k) {
+      const int len = st.off[k + 1] - st.off[k];
+      blocks += (len + bq - 1) / bq;
+      if (pre && len > 0 && few_rows(len, n_heads, n_kv_heads)) ++n_few;
+    }
     const bool paired = !pre && blocks * n_heads > 256;
     const AttnWork wk = attn_work(st, [&](int len) {
       const int nqb = (len + bq - 1) / bq;
+      if (pre && few_rows(len, n_heads, n_kv_heads)) return 0;
       return paired ? (nqb + 1) / 2 : nqb;
     });
-    if (wk.total == 0) return hipSuccess;
+    if (wk.total == 0 && n_few == 0) return hipSuccess;
     // the buffer descriptor covers one sequence's rows with 32-bit byte offsets
     if ((int64_t)st.max_len * ldq * 2 >= ((int64_t)1 << 31) || n_heads % n_kv_heads != 0) return hipErrorInvalidValue;
     const int grp = n_heads / n_kv_heads;
@@ -771,15 +781,14 @@ hipError_t launch_attention(const void* qkv, int64_t ldq, void* out, int64_t ldo
     KvPrefix pk{};
     if (pre) {
       pk = *prefix;
-      if (pk.pos && !attention_takes_positions(st, n_heads, n_kv_heads, head_dim, pk.P, pk.full_P,
-                                               std::max(pk.ldk, pk.ldv)))
+      if (pk.pos && !attention_takes_positions(st, n_heads, n_kv_heads, pk.P, pk.full_P, std::max(pk.ldk, pk.ldv)))
         return hipErrorInvalidValue;
       // one descriptor per sequence's cached prefix, also with 32-bit byte offsets
       const int64_t ld = std::max(std::max(pk.ldk, pk.ldv), pk.alt_pass >= 0 && pk.n_seq > 0 ? pk.ldv_alt : 0);
       if ((int64_t)pk.P * ld * 2 >= ((int64_t)1 << 31)) return hipErrorInvalidValue;
       if (pk.n_seq > 0 && (st.n % pk.n_seq != 0 || (pk.alt_pass >= 0 && !pk.v_alt))) return hipErrorInvalidValue;
     }
-    if (pre && few_rows(st, n_heads, n_kv_heads)) {
+    if (n_few > 0) {
       if (head_dim == 128)
         attn_few_kernel<128><<<st.n * n_kv_heads, 256, 0, s>>>((const bf16_t*)qkv, ldq, (bf16_t*)out, ldo, st, n_heads,
                                                                n_kv_heads, pk);
@@ -787,7 +796,7 @@ hipError_t launch_attention(const void* qkv, int64_t ldq, void* out, int64_t ldo
         attn_few_kernel<64><<<st.n * n_kv_heads, 256, 0, s>>>((const bf16_t*)qkv, ldq, (bf16_t*)out, ldo, st, n_heads,
                                                               n_kv_heads, pk);
       else return hipErrorInvalidValue;
-      return hipGetLastError();
+      if (wk.total == 0) return hipGetLastError();
     }
 #define RK_ATTN(D, PRE)                                                                                      \
   attn_bf16_kernel<D, PRE><<<grid, 64 * AttnTraits<D>::kWaves, 0, s>>>((const bf16_t*)qkv, ldq, (bf16_t*)out, ldo, \

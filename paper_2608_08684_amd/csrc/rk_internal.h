@@ -136,8 +136,7 @@ struct KvPrefix {
 };
 // Whether the attention of these rows behind a cached prefix reads retained positions
 // (keep per KV head, of full_P rows of ld elements) in place: few query rows.
-bool attention_takes_positions(const SeqTable& st, int n_heads, int n_kv_heads, int head_dim, int keep, int full_P,
-                               int64_t ld);
+bool attention_takes_positions(const SeqTable& st, int n_heads, int n_kv_heads, int keep, int full_P, int64_t ld);
 
 hipError_t launch_attention(const void* qkv, int64_t ldq, void* out, int64_t ldo, const SeqTable& st,
                             int n_heads, int n_kv_heads, int head_dim, bool bf16, hipStream_t s,
