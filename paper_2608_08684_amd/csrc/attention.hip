@@ -589,6 +589,56 @@ __global__ __launch_bounds__(256) void attn_few_kernel(const bf16_t* __restrict_
   }
 }
 
+// infinite or NaN, by its bits (opaque to the compiler, which takes floats here not to be NaN)
+__device__ __forceinline__ bool nonfinite(float x) {
+  uint32_t bits = __builtin_bit_cast(uint32_t, x);
+  asm volatile("" : "+v"(bits));
+  return (bits & 0x7f800000u) == 0x7f800000u;
+}
+
+// fp32, one row of a sequence (rows at base) and head, key by key: lane sub of eight holds the
+// dimensions 4 sub + 32 j .. + 3.  hq, hk, hv: the head's places in a row, in heads.
+template <int DH>
+__device__ __forceinline__ void attn_f32_row(const float* base, int64_t ldq, int row, int hq, int hk, int hv,
+                                             float scale, int sub, float* op) {
+  constexpr int N = DH / 32;
+  f32x4_t q[N], acc[N];
+#pragma unroll
+  for (int j = 0; j < N; ++j) {
+    q[j] = *reinterpret_cast<const f32x4_t*>(base + (int64_t)row * ldq + hq * DH + j * 32 + sub * 4);
+    acc[j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+  }
+  float m = -INFINITY, l = 0.f;
+  for (int u = 0; u <= row; ++u) {
+    const float* kp = base + (int64_t)u * ldq + hk * DH + sub * 4;
+    const float* vp = base + (int64_t)u * ldq + hv * DH + sub * 4;
+    float s = 0.f;
+#pragma unroll
+    for (int j = 0; j < N; ++j) {
+      const f32x4_t kf = *reinterpret_cast<const f32x4_t*>(kp + j * 32);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) s = fmaf(q[j][e], kf[e], s);
+    }
+#pragma unroll
+    for (int x = 1; x < 8; x <<= 1) s += __shfl_xor(s, x, 64);
+    s *= scale;
+    const float m_new = fmaxf(m, s), corr = expf(m - m_new), p = expf(s - m_new);
+    l = l * corr + p;
+    m = m_new;
+#pragma unroll
+    for (int j = 0; j < N; ++j) {
+      const f32x4_t vf = *reinterpret_cast<const f32x4_t*>(vp + j * 32);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) acc[j][e] = fmaf(p, vf[e], acc[j][e] * corr);
+    }
+  }
+  const float inv = 1.0f / l;
+#pragma unroll
+  for (int j = 0; j < N; ++j)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) op[j * 32 + sub * 4 + e] = acc[j][e] * inv;
+}
+
 // fp32: one workgroup = 4 waves for 32 queries of one head.  The waves share out the
 // 32-key blocks (wave w takes blocks w, w + 4, ...), each with its own running
 // maximum, denominator and output, merged through LDS in wave order.  S^T = K Q^T and
@@ -599,13 +649,16 @@ __global__ __launch_bounds__(256) void attn_few_kernel(const bf16_t* __restrict_
 // Bound: latency of a block's two MFMA chains (2 x d_h x 32 cycles) and of its loads.
 // Against one thread per (row, head) walking the keys: 256 rows, 4 heads of 64 276 us,
 // 1024 + 777 rows, 12 heads of 64 1216 us.
-template <int DH>
-__global__ __launch_bounds__(256) void attn_f32_kernel(const float* __restrict__ qkv, int64_t ldq,
-                                                       float* __restrict__ out, int64_t ldo, SeqTable st, AttnWork wk,
-                                                       int H, int Hkv, float scale) {
+// CLEAN: Values of the diagonal block that are infinite or NaN (tested by their bits: this
+// file is compiled as if there were no NaN) count as zero, and the rows from the first of
+// them on, which see it, are walked key by key.  Returns whether any of the thread's
+// outputs is infinite or NaN.
+template <int DH, bool CLEAN>
+__device__ __forceinline__ bool attn_f32_tile(const float* __restrict__ qkv, int64_t ldq, float* __restrict__ out,
+                                              int64_t ldo, const SeqTable& st, const AttnWork& wk, int H, int Hkv,
+                                              float scale, float (&so)[4][32 * (DH + 4)], float (&sm)[4][32],
+                                              float (&sl)[4][32], int32_t& sbad) {
   constexpr int HD = DH / 2, NDB = DH / 32, SP = DH + 4;
-  __shared__ __attribute__((aligned(16))) float so[4][32 * SP];
-  __shared__ float sm[4][32], sl[4][32];
   const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, hf = lane >> 5;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int item = blockIdx.x / H, hq = blockIdx.x - item * H, hk = hq / (H / Hkv);
@@ -670,8 +723,23 @@ __global__ __launch_bounds__(256) void attn_f32_kernel(const float* __restrict__
     for (int i = 0; i < 16; ++i) {
       const float* vp = vbase + (int64_t)min(k0 + (i >> 2) * 8 + hf * 4 + (i & 3), T - 1) * ldq + l32;
 #pragma unroll
-      for (int db = 0; db < NDB; ++db) o[db] = __builtin_amdgcn_mfma_f32_32x32x2f32(vp[db * 32], s[i], o[db], 0, 0, 0);
+      for (int db = 0; db < NDB; ++db) {
+        float x = vp[db * 32];
+        if constexpr (CLEAN)
+          if (kb == qb && nonfinite(x)) x = 0.f;
+        o[db] = __builtin_amdgcn_mfma_f32_32x32x2f32(x, s[i], o[db], 0, 0, 0);
+      }
     }
+    if constexpr (CLEAN)
+      if (kb == qb) {   // one wave's
+        int first = INT32_MAX;
+        for (int u = min(k0 + 31, T - 1); u >= k0; --u) {
+          bool bad = false;
+          for (int j = lane; j < DH; j += 64) bad |= nonfinite(vbase[(int64_t)u * ldq + j]);
+          if (__any(bad)) first = u;
+        }
+        if (lane == 0) sbad = first;
+      }
   }
   l = sum_halves(l);
   if (hf == 0) {
@@ -686,7 +754,7 @@ __global__ __launch_bounds__(256) void attn_f32_kernel(const float* __restrict__
           f32x4_t{o[db][4 * g], o[db][4 * g + 1], o[db][4 * g + 2], o[db][4 * g + 3]};
   __syncthreads();
   const int q = tid >> 3, row = q0 + q;
-  if (row >= T) return;
+  if (row >= T) return false;
   float M = sm[0][q];   // wave 0 holds block 0: finite
 #pragma unroll
   for (int j = 1; j < 4; ++j) M = fmaxf(M, sm[j][q]);
@@ -698,6 +766,7 @@ __global__ __launch_bounds__(256) void attn_f32_kernel(const float* __restrict__
   }
   const float inv = 1.0f / L;
   float* op = out + (int64_t)(row0 + row) * ldo + (int64_t)hq * DH;
+  bool bad = false;
 #pragma unroll
   for (int c = (tid & 7) * 4; c < DH; c += 32) {
     f32x4_t a = {0.f, 0.f, 0.f, 0.f};
@@ -708,9 +777,28 @@ __global__ __launch_bounds__(256) void attn_f32_kernel(const float* __restrict__
       for (int e = 0; e < 4; ++e) a[e] += x[e] * f[j];
     }
 #pragma unroll
-    for (int e = 0; e < 4; ++e) a[e] *= inv;
+    for (int e = 0; e < 4; ++e) {
+      a[e] *= inv;
+      bad |= nonfinite(a[e]);
+    }
     *reinterpret_cast<f32x4_t*>(op + c) = a;
   }
+  if constexpr (CLEAN)
+    if (row >= sbad) attn_f32_row<DH>(qkv + (int64_t)row0 * ldq, ldq, row, hq, H + hk, H + Hkv + hk, scale, tid & 7, op);
+  return bad;
+}
+
+template <int DH>
+__global__ __launch_bounds__(256) void attn_f32_kernel(const float* __restrict__ qkv, int64_t ldq,
+                                                       float* __restrict__ out, int64_t ldo, SeqTable st, AttnWork wk,
+                                                       int H, int Hkv, float scale) {
+  __shared__ __attribute__((aligned(16))) float so[4][32 * (DH + 4)];
+  __shared__ float sm[4][32], sl[4][32];
+  __shared__ int32_t sbad;
+  const bool bad = attn_f32_tile<DH, false>(qkv, ldq, out, ldo, st, wk, H, Hkv, scale, so, sm, sl, sbad);
+  // A masked key's zero weight times a non-finite Value is NaN, which would reach rows that do
+  // not see the key: such a tile is run again.
+  if (__syncthreads_or(bad)) attn_f32_tile<DH, true>(qkv, ldq, out, ldo, st, wk, H, Hkv, scale, so, sm, sl, sbad);
 }
 
 // Work items of a launch: sequences by decreasing length; items[k] per sequence.
