@@ -311,12 +311,13 @@ __device__ __forceinline__ void tile_lse(const f32x16_t (&acc)[G::MI][G::NI], fl
 #pragma unroll
       for (int i = 0; i < 16; ++i) m = fmaxf(m, acc[mi][ni][i]);
     m = fmaxf(m, __shfl_xor(m, 32, 64));   // the half-waves hold the same rows
+    // from the exact difference: e^(x - m) as 2^(x log2 e - m log2 e) would carry the rounding of m log2 e,
+    // as large as that of the whole log-sum-exp to fp32
     float z = 0.f;
-    const float ml = m * kLog2e;
 #pragma unroll
     for (int ni = 0; ni < G::NI; ++ni)
 #pragma unroll
-      for (int i = 0; i < 16; ++i) z += __builtin_amdgcn_exp2f(fmaf(acc[mi][ni][i], kLog2e, -ml));
+      for (int i = 0; i < 16; ++i) z += __builtin_amdgcn_exp2f((acc[mi][ni][i] - m) * kLog2e);
     z += __shfl_xor(z, 32, 64);
     if (lane < 32) red[(wm * G::WTM + mi * 32 + lane) * NWN + wn] = make_float2(m, z);
   }

@@ -204,3 +204,44 @@ def test_clean_log_sum_exp(d, vocab, lengths):
     err = (lse - want).abs().max().item()
     print(f"d {d} vocab {vocab} rows {rows}: log-sum-exp off by {err:.2e}")
     assert err < 1e-5
+
+
+# Logits far from zero (up to +-1032, exact in fp32: signed sums of powers of two and of multiples of 1/16, from
+# embeddings of +-1 through blocks whose output weights are zero).  e^(x - max) of such logits is formed from the exact
+# difference, so the log-sum-exp is off by its rounding to fp32 and by the rounding of the terms (exp2 1 ulp, 256 terms per
+# column block: a few 1e-7), whatever the size of the maximum; scaled before the subtraction, the maximum alone would put
+# it off by up to 4e-5
+def test_clean_log_sum_exp_of_large_logits():
+    import numpy as np
+    import torch
+    import paper_2608_08684_amd as rk
+    d, vocab, rows = 256, 512, 300
+    m = Shape(d, 2, 1, 64, 64, vocab=vocab)
+    g = torch.Generator(device="cuda").manual_seed(11)
+    mat = lambda r, c: torch.empty(r, c, device="cuda", dtype=torch.bfloat16).normal_(0, c ** -0.5, generator=g)
+    zero = lambda r, c: torch.zeros(r, c, device="cuda", dtype=torch.bfloat16)
+    one = torch.ones(d, device="cuda")
+    gain = torch.cat([2.0 ** torch.arange(9, 1, -1), torch.randint(0, 128, (d - 8,)) / 16.0]).float().cuda()
+    sign = lambda *shape: (torch.randint(0, 2, shape, device="cuda", generator=g) * 2 - 1).to(torch.bfloat16)
+    head = zero(vocab, d)
+    head[:, :8] = 1.0
+    head[torch.arange(vocab), 8 + torch.arange(vocab) % (d - 8)] = 1.0
+    w = {"tok_emb": sign(vocab, d), "lm_head": head, "final_norm": gain, "attn_norm": [one] * 2, "mlp_norm": [one] * 2,
+         "w_qkv": [mat(256, d)] * 2, "w_o": [zero(d, 128)] * 2, "w_gate_up": [mat(128, d)] * 2, "w_down": [zero(d, 64)] * 2}
+    model = rk.Model(m, w)
+    tok = torch.randperm(vocab, device="cuda", generator=g)[:rows].to(torch.int32)
+    batch = rk.Batch(tok, [0, rows])
+    state = torch.full((model.clean_state_size(rows),), 0xFF, dtype=torch.uint8, device="cuda")
+    ws = torch.full((model.workspace_size(rows, 1, 0),), 0xFF, dtype=torch.uint8, device="cuda")
+    model.reference_forward(batch, state, ws)
+    up = lambda n: (n + 255) // 256 * 256
+    x0 = up(2 * rows * d * 4)
+    l0 = x0 + up(up(rows) * d * 2)
+    x = state[x0:x0 + rows * d * 2].view(torch.bfloat16).view(rows, d).double()
+    assert torch.equal(x, w["tok_emb"][tok.long()].double() * gain.double())
+    lse = state[l0:l0 + rows * 4].view(torch.float32).double().cpu().numpy()
+    want = torch.logsumexp(x @ head.double().t(), dim=1).cpu().numpy()
+    err = np.abs(lse - want)
+    assert np.abs(want).max() > 500
+    print(f"log-sum-exp up to {np.abs(want).max():.0f}: off by {err.max():.2e}")
+    assert (err <= 0.5 * np.spacing(np.abs(want).astype(np.float32)) + 2e-6).all()
