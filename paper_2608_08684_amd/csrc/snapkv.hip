@@ -35,12 +35,14 @@
 namespace rk {
 
 constexpr int kSnapChunk = 256;   // keys per step of the scoring kernels (4 waves x 64)
-// Chunks per workgroup of the scoring kernels: the query tile (up to 70 KB) is staged once
-// for four chunks, with four loads per thread in flight.  8 layers of 4 x 8192 keys, 8 KV
-// heads of 128: statistics 226 -> 202 us, votes 177 -> 163 (with the masks and the exact
-// exp2 off the prefix blocks' path).  Neither is bound by how the Keys are read: through
-// a coalesced LDS ring, or from the last-level cache, they took the same time.
-constexpr int kSnapGroup = 4;
+// Chunks per workgroup of the scoring kernels: two, which stage the query tile (up to 70 KB)
+// once and load the second chunk's Keys under the first one's end, where single chunks are
+// four workgroups per CU or more; with fewer the second chunk only makes the call longer.
+// Statistics, norm and votes of 8 layers x 8 KV heads of 128, single / two: 4 x 8192 keys 361 /
+// 321 us, 4096 keys (1024 workgroups) 62.6 / 58, 2048 keys 40 / 43; 1 layer of 1000 keys
+// 26 / 35 (always four: 376, 75, 65 and 59).  At 8 layers x 12 KV heads of 64, one query head
+// each: 8192 keys 59 / 58, 1000 keys 18.6 / 19.6.
+constexpr int kSnapPairFrom = 1024;
 
 // Observation-query tile in LDS: row r (combination c = r / 32 of query head and
 // 32-query block, query j = r % 32) holds CH = d_h / 8 16-byte chunks padded to
@@ -57,13 +59,12 @@ __device__ __forceinline__ bf16x8_t kfrag(const bf16_t* krow, int ks, int lane) 
 }
 
 // Stage the observation queries of KV head g of sequence i into LDS: combos =
-// group * nqb rows of 32 queries (rows past w are zero).
-template <int DH>
+// group * nqb rows of 32 queries (rows past w are zero); U loads of a thread in flight.
+template <int DH, int U>
 __device__ __forceinline__ void load_qobs(v4u* qt, const bf16_t* qobs, int64_t ldq, int i, int g, int w, int group,
                                           int nqb) {
   constexpr int CH = DH / 8;
   const int rows = group * nqb * 32;
-  constexpr int U = 4;   // loads in flight per thread
   for (int s0 = threadIdx.x; s0 < rows * CH; s0 += U * 256) {
     v4u val[U];
 #pragma unroll
@@ -91,15 +92,17 @@ struct SnapLayers {
   int64_t kv_stride, q_stride;   // elements
 };
 
+// Waves per SIMD (here and in the votes): without the limit the compiler takes registers for
+// one wave fewer (8 layers of 32768 keys, 12 KV heads of 64: 247 -> 221 us for both).
 template <int DH>
-__global__ __launch_bounds__(256) void snap_stats_kernel(const bf16_t* __restrict__ kv, int64_t ldkv,
+__global__ __launch_bounds__(256, DH == 64 ? 4 : 3) void snap_stats_kernel(const bf16_t* __restrict__ kv, int64_t ldkv,
                                                          const bf16_t* __restrict__ qobs, int64_t ldq, SeqTable st,
-                                                         int w, int n_heads, int n_kv, int nchunks, SnapLayers ly,
+                                                         int w, int n_heads, int n_kv, int nchunks, int per, SnapLayers ly,
                                                          float2* __restrict__ part) {
   constexpr int NKS = DH / 16, MAXC = 8;
   extern __shared__ v4u qt[];
   __shared__ float2 red[4][MAXC][32];
-  const int c0 = blockIdx.x * kSnapGroup, g = blockIdx.y, l = blockIdx.z / st.n, i = blockIdx.z % st.n;
+  const int c0 = blockIdx.x * per, g = blockIdx.y, l = blockIdx.z / st.n, i = blockIdx.z % st.n;
   const int T = st.off[i + 1] - st.off[i], row0 = st.off[i];
   if (c0 * kSnapChunk >= T) return;
   kv += l * ly.kv_stride;
@@ -107,20 +110,25 @@ __global__ __launch_bounds__(256) void snap_stats_kernel(const bf16_t* __restric
   part += (int64_t)l * st.n * n_heads * w * nchunks;
   const int group = n_heads / n_kv, nqb = (w + 31) >> 5, combos = group * nqb;
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, l32 = lane & 31;
-  load_qobs<DH>(qt, qobs, ldq, i, g, w, group, nqb);
-  __syncthreads();
-  const int c1 = min(c0 + kSnapGroup, (T + kSnapChunk - 1) / kSnapChunk);
-  for (int c = c0; c < c1; ++c) {
-  // this wave's 64 keys, both 32-key blocks in flight before the MFMAs
-  const int ub0 = c * kSnapChunk + wv * 64;
+  const int c1 = min(c0 + per, (T + kSnapChunk - 1) / kSnapChunk);
+  // this wave's 64 keys of chunk c, both 32-key blocks in flight: the first chunk's under the
+  // staging of the queries, the next one's under the merge
   bf16x8_t kf2[2][NKS];
+  auto load_keys = [&](int c) {
 #pragma unroll
-  for (int kb = 0; kb < 2; ++kb) {
-    const int uc = min(ub0 + kb * 32 + l32, T - 1);
-    const bf16_t* krow = kv + (int64_t)(row0 + uc) * ldkv + (int64_t)g * DH;
+    for (int kb = 0; kb < 2; ++kb) {
+      const int uc = min(c * kSnapChunk + wv * 64 + kb * 32 + l32, T - 1);
+      const bf16_t* krow = kv + (int64_t)(row0 + uc) * ldkv + (int64_t)g * DH;
 #pragma unroll
-    for (int ks = 0; ks < NKS; ++ks) kf2[kb][ks] = kfrag(krow, ks, lane);
-  }
+      for (int ks = 0; ks < NKS; ++ks) kf2[kb][ks] = kfrag(krow, ks, lane);
+    }
+  };
+  load_keys(c0);
+  if (combos >= 4) load_qobs<DH, 4>(qt, qobs, ldq, i, g, w, group, nqb);
+  else load_qobs<DH, 1>(qt, qobs, ldq, i, g, w, group, nqb);
+  __syncthreads();
+  for (int c = c0; c < c1; ++c) {
+  const int ub0 = c * kSnapChunk + wv * 64;
   float m[MAXC], z[MAXC];
 #pragma unroll
   for (int q = 0; q < MAXC; ++q) { m[q] = -INFINITY; z[q] = 0.f; }
@@ -164,6 +172,7 @@ __global__ __launch_bounds__(256) void snap_stats_kernel(const bf16_t* __restric
       }
     }
   }
+  if (c + 1 < c1) load_keys(c + 1);
   // the two half-waves hold the same queries (different keys); then the 4 waves
 #pragma unroll
   for (int q = 0; q < MAXC; ++q) {
@@ -209,15 +218,15 @@ __global__ void snap_norm_kernel(const float2* __restrict__ part, SeqTable st, i
 }
 
 template <int DH>
-__global__ __launch_bounds__(256) void snap_votes_kernel(const bf16_t* __restrict__ kv, int64_t ldkv,
+__global__ __launch_bounds__(256, DH == 64 ? 6 : 4) void snap_votes_kernel(const bf16_t* __restrict__ kv, int64_t ldkv,
                                                          const bf16_t* __restrict__ qobs, int64_t ldq, SeqTable st,
-                                                         int w, int n_heads, int n_kv, SnapLayers ly,
+                                                         int w, int n_heads, int n_kv, int per, SnapLayers ly,
                                                          const float* __restrict__ cnorm, float* __restrict__ votes,
                                                          int64_t prefix_rows) {
   constexpr int NKS = DH / 16, MAXC = 8;
   extern __shared__ v4u qt[];
   __shared__ float cinit[MAXC * 32];
-  const int c0 = blockIdx.x * kSnapGroup, g = blockIdx.y, l = blockIdx.z / st.n, i = blockIdx.z % st.n;
+  const int c0 = blockIdx.x * per, g = blockIdx.y, l = blockIdx.z / st.n, i = blockIdx.z % st.n;
   const int T = st.off[i + 1] - st.off[i], row0 = st.off[i], npre = T - w;
   if (c0 * kSnapChunk >= npre) return;
   kv += l * ly.kv_stride;
@@ -226,7 +235,20 @@ __global__ __launch_bounds__(256) void snap_votes_kernel(const bf16_t* __restric
   votes += (int64_t)l * n_kv * prefix_rows;
   const int group = n_heads / n_kv, nqb = (w + 31) >> 5, combos = group * nqb;
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, l32 = lane & 31;
-  load_qobs<DH>(qt, qobs, ldq, i, g, w, group, nqb);
+  const int c1 = min(c0 + per, (npre + kSnapChunk - 1) / kSnapChunk);
+  bf16x8_t kf2[2][NKS];
+  auto load_keys = [&](int c) {
+#pragma unroll
+    for (int kb = 0; kb < 2; ++kb) {
+      const int uc = min(c * kSnapChunk + wv * 64 + kb * 32 + l32, npre - 1);
+      const bf16_t* krow = kv + (int64_t)(row0 + uc) * ldkv + (int64_t)g * DH;
+#pragma unroll
+      for (int ks = 0; ks < NKS; ++ks) kf2[kb][ks] = kfrag(krow, ks, lane);
+    }
+  };
+  load_keys(c0);   // under the staging of the queries
+  if (combos >= 4) load_qobs<DH, 4>(qt, qobs, ldq, i, g, w, group, nqb);
+  else load_qobs<DH, 1>(qt, qobs, ldq, i, g, w, group, nqb);
   for (int idx = threadIdx.x; idx < combos * 32; idx += blockDim.x) {
     const int q = idx >> 5, jj = (q % nqb) * 32 + (idx & 31);
     const int h = g * group + q / nqb;
@@ -234,16 +256,9 @@ __global__ __launch_bounds__(256) void snap_votes_kernel(const bf16_t* __restric
   }
   __syncthreads();
   const int64_t pre0 = (int64_t)row0 - (int64_t)i * w;   // first prefix row of sequence i in the votes
-  const int c1 = min(c0 + kSnapGroup, (npre + kSnapChunk - 1) / kSnapChunk);
   for (int c = c0; c < c1; ++c) {
+  if (c > c0) load_keys(c);
   const int ub0 = c * kSnapChunk + wv * 64;
-  bf16x8_t kf2[2][NKS];
-#pragma unroll
-  for (int kb = 0; kb < 2; ++kb) {
-    const bf16_t* krow = kv + (int64_t)(row0 + min(ub0 + kb * 32 + l32, npre - 1)) * ldkv + (int64_t)g * DH;
-#pragma unroll
-    for (int ks = 0; ks < NKS; ++ks) kf2[kb][ks] = kfrag(krow, ks, lane);
-  }
 #pragma unroll
   for (int kb = 0; kb < 2; ++kb) {
     const int ub = ub0 + kb * 32;
@@ -491,13 +506,16 @@ hipError_t launch_snap_scores(const void* kv, int64_t ldkv, int64_t kv_layer_str
   const int combos = (n_heads / n_kv) * ((w + 31) / 32);
   const size_t lds = qtile_bytes(head_dim, combos);
   const SnapLayers ly{kv_layer_stride, q_layer_stride};
-  dim3 grid((nchunks + kSnapGroup - 1) / kSnapGroup, n_kv, st.n * n_layers);
+  int64_t chunks = 0;
+  for (int i = 0; i < st.n; ++i) chunks += snap_chunks(st.off[i + 1] - st.off[i]);
+  const int per = chunks * n_kv * n_layers >= kSnapPairFrom ? 2 : 1;
+  dim3 grid((nchunks + per - 1) / per, n_kv, st.n * n_layers);
   if (head_dim == 64)
     snap_stats_kernel<64><<<grid, 256, lds, s>>>((const bf16_t*)kv, ldkv, (const bf16_t*)qobs, ldq, st, w, n_heads,
-                                                 n_kv, nchunks, ly, part);
+                                                 n_kv, nchunks, per, ly, part);
   else if (head_dim == 128)
     snap_stats_kernel<128><<<grid, 256, lds, s>>>((const bf16_t*)kv, ldkv, (const bf16_t*)qobs, ldq, st, w, n_heads,
-                                                  n_kv, nchunks, ly, part);
+                                                  n_kv, nchunks, per, ly, part);
   else
     return hipErrorInvalidValue;
   hipError_t e = hipGetLastError();
@@ -507,10 +525,10 @@ hipError_t launch_snap_scores(const void* kv, int64_t ldkv, int64_t kv_layer_str
   if ((e = hipGetLastError()) != hipSuccess) return e;
   if (head_dim == 64)
     snap_votes_kernel<64><<<grid, 256, lds, s>>>((const bf16_t*)kv, ldkv, (const bf16_t*)qobs, ldq, st, w, n_heads,
-                                                 n_kv, ly, cnorm, votes, prefix_rows);
+                                                 n_kv, per, ly, cnorm, votes, prefix_rows);
   else
     snap_votes_kernel<128><<<grid, 256, lds, s>>>((const bf16_t*)kv, ldkv, (const bf16_t*)qobs, ldq, st, w, n_heads,
-                                                  n_kv, ly, cnorm, votes, prefix_rows);
+                                                  n_kv, per, ly, cnorm, votes, prefix_rows);
   return hipGetLastError();
 }
 

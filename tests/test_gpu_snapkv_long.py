@@ -84,3 +84,47 @@ def test_scores_and_selection(heads, kv_heads, dh, lens, w, kernel, average):
                 assert torch.equal(vo[e:e + keep], v[sel])
     print(f"votes off by {worst:.2e} at most")
     assert worst < 3e-5
+
+
+@pytest.mark.parametrize("heads, kv_heads, dh, lens, w, layers", [
+    (8, 8, 64, [4096 + 32, 700], 32, 8),        # 17 and 3 chunks: 1280 workgroups of one, so two per workgroup
+    (8, 2, 128, [8192 + 256 + 1, 513], 32, 16),   # a chunk of one key; 1184
+])
+def test_votes_of_chunk_pairs(heads, kv_heads, dh, lens, w, layers):
+    """Two chunks per workgroup (all layers in one call) and one (a model of a single layer) vote bitwise the same."""
+    import torch
+    import paper_2608_08684_amd as rk
+    n, R = len(lens), sum(lens)
+    offs = [sum(lens[:i]) for i in range(n + 1)]
+    g = torch.Generator(device="cuda").manual_seed(5)
+    kv = torch.empty(layers, R, 2 * kv_heads * dh, dtype=torch.bfloat16, device="cuda").normal_(generator=g)
+    q = torch.empty(layers, n * w, heads * dh, dtype=torch.bfloat16, device="cuda").normal_(
+        0, 2.5 / math.sqrt(dh), generator=g)
+    batch = rk.Batch(torch.zeros(R, dtype=torch.int32, device="cuda"), offs)
+
+    def votes(kv, q):
+        m = Cfg(heads, kv_heads, dh)
+        m.n_layers = L = kv.shape[0]
+        one = torch.zeros(128, device="cuda")
+        weights = {k: one for k in ("tok_emb", "lm_head", "final_norm")}
+        weights.update({k: [one] * L for k in ("w_qkv", "w_o", "w_gate_up", "w_down", "attn_norm", "mlp_norm")})
+        model = rk.Model(m, weights)
+        state = torch.zeros(model.snapkv_state_size(R, n, w), dtype=torch.uint8, device="cuda")
+        kvb = kv.numel() * 2
+        state[:kvb].copy_(kv.contiguous().view(torch.uint8).reshape(-1))
+        q0 = (kvb + 255) // 256 * 256
+        state[q0:q0 + q.numel() * 2].copy_(q.contiguous().view(torch.uint8).reshape(-1))
+        budgets = [[w + 1] * L] * n
+        total, _ = rk.snapkv_layout(batch, L, budgets)
+        pos = torch.empty(kv_heads * total, dtype=torch.int32, device="cuda")
+        ko, vo = (torch.empty(kv_heads * total, dh, dtype=torch.bfloat16, device="cuda") for _ in range(2))
+        sc = torch.empty(L, kv_heads, R - n * w, device="cuda")
+        ws = torch.full((model.snapkv_workspace_size(R, n, w),), 0xFF, dtype=torch.uint8, device="cuda")
+        model.snapkv_compress(batch, budgets, state, pos, ko, vo, ws, obs_window=w, pool_kernel=1,
+                              pooling=rk.RK_POOL_MAX, scores=sc)
+        torch.cuda.synchronize()
+        return sc
+
+    both = votes(kv, q)
+    for l in range(layers):
+        assert torch.equal(both[l], votes(kv[l:l + 1], q[l:l + 1])[0]), l
