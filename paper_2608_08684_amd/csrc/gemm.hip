@@ -698,22 +698,25 @@ static int cu_count() {
   return n;
 }
 
-// The tile with the least estimated time.  A launch takes
-//   rounds x (fixed + k-steps x step)   microseconds,
-// rounds = tiles / (CUs x workgroups per CU) rounded up; the constants are fits
-// (within about 15%) to times measured over M = 16 .. 65536 at the widths 256, 768, 4096.
+// The tile with the least estimated time.  A round of workgroups takes fixed + k-steps x step
+// microseconds, a ring tile's last round by how many tiles are left in it, an 8-wave tile's every
+// round alike; the constants are fits to launches inside clean passes (weights and rows from
+// memory), M = 17 .. 24576 at the widths 768 and 4096.  There the tile taken is the best at nine
+// sizes of ten and within 25% of it at all, and its estimate within 6% at half of them, 20% at
+// nine of ten and 40% at all.  Fits to single launches, and every round of ring tiles counted as
+// full, put 32x64 and 64x64 where rounds of them wait on L2: 768 rows, N = 4096, K = 14336
+// 257 us (now 199), 512 rows, N = 6144, K = 4096 75.7 (60), 4096 rows, N = 768, K = 3072 57 (43),
+// 4608 rows, N = K = 768 23 (20); two LM heads of 48 rows, N = 128256, K = 4096 400 (272).
 // The 8-wave tiles: 256x256 fixed 11.5, step 0.89 with a few tiles, up to 1.25 with every
-// CU busy; 256x192 11 and 0.78; 256x128 7.5 and 0.61 (1000 rows, N = 6144, K = 4096: 73, -,
-// 55 us; 2048 rows: 91, -, 114).  The ring tiles: 64x128 4.4 and 0.285; two workgroups
-// per CU: 64x64 3 and 0.195, 0.36 for two together, 32x64 3 and 0.13, 0.17, 32x32 3 and
-// 0.108, 0.13 (16 rows, N = 4096, K = 14336: 66, 45, 33, 27 us; 509 rows, N = 768, K = 3072:
-// 16, 11.9, 9.1, 10.6).  No tile beats the time the weights take from memory (5.5 TB/s);
-// among equals the one listed first is taken.
+// CU busy; 256x192 11 and 0.78; 256x128 7.5 and 0.61.  The ring tiles: 64x128 2.5, 0.3 and up to
+// 0.39; two workgroups per CU, step with one and with both: 64x64 1.4, 0.28, 0.52; 32x64
+// 0.65, 0.22, 0.36; 32x32 1.2, 0.15, 0.24.  No tile beats the time the weights take from
+// memory (4.9 TB/s); among equals the one listed first is taken.
 enum class Tile { k32x16, k32x64, k32x32, k64x64, k64x128, k256x128, k256x192, k256x256 };
 
 static Tile pick_tile(const GemmArgs& a, bool swiglu) {
   const int64_t ncu = cu_count(), nk = a.K / kBK;
-  const double mem = (double)a.N * a.K * 2 / 5.5e6;   // microseconds
+  const double mem = (double)a.N * a.K * 2 / 4.9e6;   // microseconds
   double best = 1e30;
   Tile tile = Tile::k32x64;
   auto offer = [&](Tile t, double us) {
@@ -721,24 +724,27 @@ static Tile pick_tile(const GemmArgs& a, bool swiglu) {
     if (us < best) { best = us; tile = t; }
   };
   auto tiles = [&](int bm, int bn) { return ((a.M + bm - 1) / bm) * (int64_t)(a.N / bn); };
-  auto rounds = [&](int64_t n, int64_t per) { return (double)((n + per - 1) / per); };
-  auto two = [&](Tile t, int bm, int bn, double alone, double both) {   // two workgroups per CU
-    const int64_t n = tiles(bm, bn);
-    offer(t, rounds(n, 2 * ncu) * (3.0 + nk * (n <= ncu ? alone : both)));
+  // ring tiles, `per` workgroups per CU: full rounds, and one of the tiles left
+  auto ring = [&](Tile t, int bm, int bn, int per, double fixed, double alone, double full) {
+    const int64_t n = tiles(bm, bn) * (a.A2 ? 2 : 1), nf = n / (per * ncu), rem = n % (per * ncu);
+    const double step = per == 2 ? (rem <= ncu ? alone : full) : alone + (full - alone) * ((double)rem / ncu);
+    offer(t, nf * (fixed + nk * full) + (rem ? fixed + nk * step : 0.0));
   };
   auto one = [&](Tile t, int bm, int bn, double fixed, double step, double load) {
     const int64_t n = tiles(bm, bn);
-    offer(t, rounds(n, ncu) * (fixed + nk * step * (1.0 + load * (n < ncu ? (double)n / ncu : 1.0))));
+    const double rounds = (double)((n + ncu - 1) / ncu);
+    const double us = rounds * (fixed + nk * step * (1.0 + load * (n < ncu ? (double)n / ncu : 1.0)));
+    offer(t, a.A2 ? 2.0 * std::max(us, mem) : us);   // a launch for each set of rows
   };
   // 32x16 tiles put twice the CUs on weights that stream from memory; worth it where K is
   // long enough for their 24-stage ring (16 rows, N = 4096, cold weights: K = 14336 41.6 -> 37
   // us, K = 4096 12.6 -> 14.2; a decode step of 8 blocks 1.41 -> 1.38 ms)
   if (nk >= 128 && tiles(32, 16) <= ncu) one(Tile::k32x16, 32, 16, 3.0, 0.1, 0.0);
-  two(Tile::k32x64, 32, 64, 0.13, 0.17);
-  two(Tile::k32x32, 32, 32, 0.108, 0.13);
-  two(Tile::k64x64, 64, 64, 0.195, 0.36);
+  ring(Tile::k32x64, 32, 64, 2, 0.65, 0.22, 0.36);
+  ring(Tile::k32x32, 32, 32, 2, 1.2, 0.15, 0.24);
+  ring(Tile::k64x64, 64, 64, 2, 1.4, 0.28, 0.52);
   // a 64-wide run does not fit a 64-wide head's half
-  if (a.epi != Epi::kStoreRope || a.head_dim == 128) one(Tile::k64x128, 64, 128, 4.4, 0.285, 0.0);
+  if (a.epi != Epi::kStoreRope || a.head_dim == 128) ring(Tile::k64x128, 64, 128, 1, 2.5, 0.3, 0.39);
   one(Tile::k256x128, 256, 128, 7.5, 0.61, 0.4);
   // 192-wide tiles have three column blocks per wave: no pairs in registers
   if (!swiglu && a.epi != Epi::kStoreRope && a.N % 192 == 0) one(Tile::k256x192, 256, 192, 11.0, 0.78, 0.4);

@@ -125,7 +125,9 @@ def test_large_tiles(m, lengths):
     (Shape(2048, 16, 8, 128, 640), [900, 101]),
     (Shape(128, 2, 1, 64, 8192), [17]),                    # long K, 16-wide tiles
     (Shape(512, 8, 2, 64, 8256), [32, 1]),
-], ids=["1row", "34", "k320", "k576", "509", "400", "2000", "wide", "k8192", "k8256"])
+    (Shape(1024, 8, 2, 128, 1088), [17]),                  # 32-wide tiles with every epilogue
+    (Shape(1024, 16, 4, 64, 2048), [64] * 17),             # a ring tile's last round partly filled
+], ids=["1row", "34", "k320", "k576", "509", "400", "2000", "wide", "k8192", "k8256", "17", "1088"])
 def test_few_rows(m, lengths):
     check_block(m, lengths)
 
@@ -154,6 +156,50 @@ def test_rows_do_not_depend_on_the_batch():
         got.append(h[1, -40:].clone())
     for x in got[1:]:
         assert torch.equal(x, got[0])
+
+
+@pytest.mark.parametrize("d, vocab, windows", [
+    (1024, 16384, [8] * 5),      # 64x128 tiles for both sets of rows, 32x64 for one sequence alone
+    (256, 16384, [9, 1, 30]),    # 64x64
+    (128, 65536, [25] * 8),      # an 8-wave tile, in a launch for each set
+])
+def test_two_sets_of_logits(d, vocab, windows):
+    """Clean and pass logits of one launch: with every cache whole they are the same rows, so the KL is exactly 0, and
+    a sequence's logits are bitwise those that it has alone."""
+    import torch
+    import paper_2608_08684_amd as rk
+    m = Shape(d, 4, 1, 64, 192, vocab=vocab)
+    g = torch.Generator(device="cuda").manual_seed(8)
+    mat = lambda r, c: torch.empty(r, c, device="cuda", dtype=torch.bfloat16).normal_(0, c ** -0.5, generator=g)
+    one = torch.ones(d, device="cuda")
+    w = {"tok_emb": mat(vocab, d), "lm_head": mat(vocab, d), "final_norm": one, "attn_norm": [one] * 2,
+         "mlp_norm": [one] * 2, "w_qkv": [mat(384, d) for _ in range(2)], "w_o": [mat(d, 256) for _ in range(2)],
+         "w_gate_up": [mat(384, d) for _ in range(2)], "w_down": [mat(d, 192) for _ in range(2)]}
+    model, P = rk.Model(m, w), 33
+    toks = [torch.randint(0, vocab, (P + t,), device="cuda", generator=g, dtype=torch.int32) for t in windows]
+    none = torch.zeros(1, dtype=torch.int32, device="cuda")
+
+    def logits(toks):
+        offs = [0]
+        for t in toks:
+            offs.append(offs[-1] + len(t))
+        batch, n = rk.Batch(torch.cat(toks), offs), len(toks)
+        flags = rk.RK_FLAG_CACHED_WINDOW | rk.RK_FLAG_UNFUSED_KL
+        state = torch.full((model.window_state_size(offs[-1]),), 0xFF, dtype=torch.uint8, device="cuda")
+        ws = torch.full((model.workspace_size(offs[-1], 1, flags),), 0xFF, dtype=torch.uint8, device="cuda")
+        model.window_reference(batch, P, state, ws)
+        rows = offs[-1] - n * P
+        out, kl = torch.empty(n, device="cuda"), torch.full((rows,), -1.0, device="cuda")
+        lg = torch.empty(rows, vocab, device="cuda")
+        model.policy_damage(batch, P, none, [0, 0], 1, [0, 0], state, out, ws, kl_pos=kl, logits_out=lg)
+        torch.cuda.synchronize()
+        assert torch.equal(kl, torch.zeros_like(kl))
+        return lg
+
+    both, r = logits(toks), 0
+    for t in toks:
+        assert torch.equal(both[r:r + len(t) - P], logits([t]))
+        r += len(t) - P
 
 
 # fp32: the same block on the fp32 tiles and the fp32 attention, head dims 32, 64 and 128, one row to several
