@@ -789,9 +789,9 @@ static hipError_t go_bf16(const GemmArgs& a, const E& e, hipStream_t s) {
   return hipGetLastError();
 }
 
-template <class E, bool SWIGLU>
-static hipError_t go(const GemmArgs& a, bool bf16, const E& e, hipStream_t s) {
-  if (bf16) {
+template <typename T, class E, bool SWIGLU>
+static hipError_t go(const GemmArgs& a, const E& e, hipStream_t s) {
+  if constexpr (sizeof(T) == 2) {
     if (E::kPaired && !SWIGLU && a.head_dim != 64 && a.head_dim != 128) return hipErrorInvalidValue;
     const Tile tile = pick_tile(a, SWIGLU);
     // the 8-wave tiles take the second rows (the LM head only) in a launch of their own
@@ -799,10 +799,10 @@ static hipError_t go(const GemmArgs& a, bool bf16, const E& e, hipStream_t s) {
       if constexpr (std::is_same<E, EpiStoreF32>::value) {
         GemmArgs one = a;
         one.A2 = nullptr;
-        hipError_t r = go<E, SWIGLU>(one, true, e, s);
+        hipError_t r = go<T, E, SWIGLU>(one, e, s);
         if (r != hipSuccess) return r;
         one.A = a.A2;
-        return go<E, SWIGLU>(one, true, EpiStoreF32{e.out2, e.ldo, nullptr}, s);
+        return go<T, E, SWIGLU>(one, EpiStoreF32{e.out2, e.ldo, nullptr}, s);
       }
       return hipErrorInvalidValue;
     }
@@ -821,10 +821,10 @@ static hipError_t go(const GemmArgs& a, bool bf16, const E& e, hipStream_t s) {
     // 64x64 tiles keep the four matrix cores of a CU busy; with fewer tiles than CUs,
     // 32x32 tiles spread the work over four times as many (a block's serial chain is
     // the same).  The two runs of a 32-wide head's halves are 16 columns.
-    const bool narrow = E::kPaired && !SWIGLU && a.head_dim < 64;
     const int64_t n64 = (int64_t)((a.M + 63) / 64) * (a.N / 64);
     if (n64 < cu_count()) return go_ring<float, 32, 32, 4, 9>(a, e, s);
-    if (narrow) return go_ring<float, 64, 32, 4, 6>(a, e, s);
+    if constexpr (E::kPaired && !SWIGLU)
+      if (a.head_dim < 64) return go_ring<float, 64, 32, 4, 6>(a, e, s);
     return go_ring<float, 64, 64, 4, 5>(a, e, s);
   }
 }
@@ -841,36 +841,23 @@ hipError_t launch_lse_tiles(const bf16_t* x, const bf16_t* W, int rows, int d, i
   return hipGetLastError();
 }
 
+template <typename T>
+static hipError_t gemm_of(const GemmArgs& a, hipStream_t s) {
+  switch (a.epi) {
+    case Epi::kStoreRope:
+      return go<T, EpiRope<T>, false>(
+          a, {(T*)a.out, a.ldo, a.rope_cols, a.head_dim, a.rope_tab, a.rope_pos, a.q_cols, a.q_scale}, s);
+    case Epi::kResidual: return go<T, EpiResidual, false>(a, {(float*)a.out, a.ldo, a.res, a.ldr}, s);
+    case Epi::kSwiGLU: return go<T, EpiSwiGLU<T>, true>(a, {(T*)a.out, a.ldo}, s);
+    case Epi::kStoreF32: return go<T, EpiStoreF32, false>(a, {(float*)a.out, a.ldo, (float*)a.out2}, s);
+  }
+  return hipErrorInvalidValue;
+}
+
 hipError_t launch_gemm(const GemmArgs& a, bool bf16, hipStream_t s) {
   if (a.M <= 0) return hipSuccess;
   if (a.A2 && a.epi != Epi::kStoreF32) return hipErrorInvalidValue;
-  switch (a.epi) {
-    case Epi::kStoreRope:
-      if (bf16) {
-        EpiRope<bf16_t> e{(bf16_t*)a.out, a.ldo, a.rope_cols, a.head_dim, a.rope_tab, a.rope_pos, a.q_cols, a.q_scale};
-        return go<EpiRope<bf16_t>, false>(a, true, e, s);
-      } else {
-        EpiRope<float> e{(float*)a.out, a.ldo, a.rope_cols, a.head_dim, a.rope_tab, a.rope_pos, a.q_cols, a.q_scale};
-        return go<EpiRope<float>, false>(a, false, e, s);
-      }
-    case Epi::kResidual: {
-      EpiResidual e{(float*)a.out, a.ldo, a.res, a.ldr};
-      return go<EpiResidual, false>(a, bf16, e, s);
-    }
-    case Epi::kSwiGLU:
-      if (bf16) {
-        EpiSwiGLU<bf16_t> e{(bf16_t*)a.out, a.ldo};
-        return go<EpiSwiGLU<bf16_t>, true>(a, true, e, s);
-      } else {
-        EpiSwiGLU<float> e{(float*)a.out, a.ldo};
-        return go<EpiSwiGLU<float>, true>(a, false, e, s);
-      }
-    case Epi::kStoreF32: {
-      EpiStoreF32 e{(float*)a.out, a.ldo, (float*)a.out2};
-      return go<EpiStoreF32, false>(a, bf16, e, s);
-    }
-  }
-  return hipErrorInvalidValue;
+  return bf16 ? gemm_of<bf16_t>(a, s) : gemm_of<float>(a, s);
 }
 
 }  // namespace rk
