@@ -102,7 +102,7 @@ def derive_traffic(fetch_dir, write_dir, copy_fetch_dir, copy_write_dir, family)
 
 # kernel families of the profile, by a substring of the kernel name (first match wins)
 FAMILIES = [("gemm_gate_up", "EpiSwiGLU"), ("gemm_qkv", "EpiRope"), ("gemm_o_down", "EpiResidual"),
-            ("lm_kl", "lm_kl_kernel"), ("lm_lse", "EpiLse"), ("attention", "attn_bf16_kernel"),
+            ("lm_kl", "lm_kl_kernel"), ("lm_lse", "EpiLse"), ("attention", "attn_"),
             ("rmsnorm", "rmsnorm_kernel"), ("noise", "value_noise_kernel"), ("kl_merge", "kl_merge_kernel"),
             ("kl_logits", "kl_logits_kernel"), ("lm_logits", "EpiStoreF32"),
             ("local_response", "local_response_kernel")]

@@ -49,3 +49,18 @@ def test_family_flops_sum_to_the_linear_work():
     d, H, dh, ff = cfg.d_model, cfg.n_heads, cfg.head_dim, cfg.d_ff
     assert per_row == 2 * d * (3 * H * dh) + 2 * H * dh * d + 4 * d * ff + 2 * ff * d
     assert np.isclose(bench.family_flops("lm_kl", cfg, 10, 3), 2 * 10 * d * cfg.vocab * 3)
+
+
+@pytest.mark.parametrize("kernel, family", [
+    ("void rk::attn_bf16_kernel<128, false>(unsigned short const*)", "attention"),
+    ("void rk::attn_few_kernel<64>(unsigned short const*)", "attention"),
+    ("void rk::attn_f32_kernel<64>(float const*)", "attention"),
+    ("void rk::gemm_alt_kernel<256, 256, 2, 4, 128, rk::EpiSwiGLU<unsigned short>, true>(...)", "gemm_gate_up"),
+    ("void rk::gemm_ring_kernel<float, 32, 32, 4, 9, rk::EpiRope<float> >(...)", "gemm_qkv"),
+    ("void rk::gemm_alt_kernel<256, 256, 2, 4, 32, rk::EpiLse, false>(...)", "lm_lse"),
+    ("void rk::rmsnorm_kernel<float, 1, 1>(...)", "rmsnorm"),
+    ("rk::window_mean_kernel(...)", None),
+])
+def test_kernel_families(kernel, family):
+    """Every attention kernel counts as attention (few query rows and fp32 have their own)."""
+    assert bench.family_of(kernel) == family
