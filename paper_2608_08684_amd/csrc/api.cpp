@@ -137,10 +137,9 @@ static WsPlan ws_plan(const rk_model* m, int64_t R, int G, uint32_t flags) {
   p.xp = o;       o += align256((size_t)G * Rp * c.d_model * a);
   p.part = o;
   if (m->bf16 && !local) {
-    // a pair per row (lm_lse), and with room lm_kl_chunks(rows) * rows <= min(n_vt * 256 * n_tb, (1024 + n_tb) * 256) for rows <= R
-    const size_t n_vt = c.vocab / 128, n_tt = (R + 127) / 128, n_tb = (R + 255) / 256;
-    const size_t bound = std::max(std::min(n_vt * 128 * n_tt, (2048 + n_tt) * 128),
-                                  std::min(n_vt * 256 * n_tb, (1024 + n_tb) * 256));
+    // a pair per row (lm_lse); lm_kl_chunks(rows) * rows <= min(n_vt * 256 * n_tb, (1024 + n_tb) * 256) for rows <= R
+    const size_t n_vt = c.vocab / 128, n_tb = (R + 255) / 256;
+    const size_t bound = std::min(n_vt * 256 * n_tb, (1024 + n_tb) * 256);
     o += align256(bound * (size_t)G * 8);
   }
   p.logits_c = o;
@@ -905,13 +904,13 @@ static rk_status window_group_final(const rk_model* m, const SeqTable& pst, cons
 // Compression damage of layer `layer` (Section 2, Eq. layer-compression-damage):
 // the window rows resume from their input to that block with its prompt cache
 // replaced by the b retained positions of every KV head (gathered into a b-row
-// cache per sequence); the caches of the other layers stay full.  The rotary
+// cache per sequence, or read in place); the caches of the other layers stay full.  The rotary
 // table must hold the window positions.
 static rk_status window_compressed_final(const rk_model* m, const SeqTable& pst, const SeqTable& wst, const Win& wn,
                                          int layer, const int32_t* pos, int64_t seq_stride, int b, void* xf_out,
                                          const Bufs& bf, hipStream_t s) {
   const rk_model_config& c = m->cfg;
-  const int64_t d = c.d_model, Rp = pst.rows, Rw = wst.rows, a = act_bytes(m), kc = kv_cols(m);
+  const int64_t d = c.d_model, Rw = wst.rows;
   KvPrefix pk{};
   rk_status e = compressed_prefix(m, wn, pst, wst, layer, pos, seq_stride, b, bf, s, &pk);
   if (e != RK_OK) return e;
@@ -928,15 +927,15 @@ static rk_status window_compressed_final(const rk_model* m, const SeqTable& pst,
 // The window rows with every layer's prompt cache compressed at once (a per-layer
 // budget policy deployed, Section 4.4): block l attends to the n_keep[l] retained
 // prompt positions of each KV head (positions + layer_off[l], per sequence at
-// seq_stride), gathered into a compressed cache, or to the whole prompt cache when
-// n_keep[l] is 0.  The window runs from block 0 (its cached input); the layers'
+// seq_stride), gathered into a compressed cache or read in place, or to the whole prompt
+// cache when n_keep[l] is 0.  The window runs from block 0 (its cached input); the layers'
 // caches are those of the full prefill.  The rotary table must hold the window
 // positions.
 static rk_status window_policy_final(const rk_model* m, const SeqTable& pst, const SeqTable& wst, const Win& wn,
                                      const int32_t* positions, const int64_t* layer_off, int64_t seq_stride,
                                      const int32_t* n_keep, void* xf_out, const Bufs& bf, hipStream_t s) {
   const rk_model_config& c = m->cfg;
-  const int64_t d = c.d_model, Rp = pst.rows, Rw = wst.rows, a = act_bytes(m), kc = kv_cols(m);
+  const int64_t d = c.d_model, Rw = wst.rows;
   const float* h_in = wn.w.h;
   for (int l = 0; l < c.n_layers; ++l) {
     KvPrefix pk{};
