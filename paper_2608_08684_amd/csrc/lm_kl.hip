@@ -41,15 +41,15 @@ __device__ __forceinline__ float kl_f(float x) {
 }
 
 // --------------------------------------------------------------------------- clean log-sum-exp
-// The chunk merges: 16 lanes per row, lane j takes chunks j, j + 16, ... in order, and a
-// fixed butterfly adds the lanes (double).  One thread per row walked all chunks, a
-// serial chain of loads: 64 us for 250 chunks of 509 rows, 526 us for 1002 of 16 rows.
+// The chunk merges: L lanes per row, lane j takes chunks j, j + L, ... in order, and a
+// fixed butterfly adds the lanes (double).  16 lanes: one thread per row walking all chunks is
+// a serial chain of loads (64 us for 250 chunks of 509 rows, 526 us for 1002 of 16 rows).
 constexpr int kMergeLanes = 16, kMergeRows = 256 / kMergeLanes;
 
-template <typename T>
+template <typename T, int L = kMergeLanes>
 __device__ __forceinline__ T merge_sum(T v) {
 #pragma unroll
-  for (int m = kMergeLanes / 2; m >= 1; m >>= 1) v += __shfl_xor(v, m, 64);
+  for (int m = L / 2; m >= 1; m >>= 1) v += __shfl_xor(v, m, 64);
   return v;
 }
 
@@ -301,18 +301,19 @@ __global__ __launch_bounds__(512) void lm_kl_kernel(const bf16_t* __restrict__ X
 }
 
 // kl[g * rows + r] = sum_c T1 + log1p(sum_c S), fixed chunk order, double.
+template <int L>
 __global__ __launch_bounds__(256) void kl_merge_kernel(const float2* __restrict__ part, int n_chunks, int G, int rows,
                                                        float* __restrict__ kl) {
-  const int r = blockIdx.x * kMergeRows + threadIdx.x / kMergeLanes, j = threadIdx.x % kMergeLanes, g = blockIdx.y;
+  const int r = blockIdx.x * (256 / L) + threadIdx.x / L, j = threadIdx.x % L, g = blockIdx.y;
   const int rr = min(r, rows - 1);
   double t1 = 0.0, s = 0.0;
-  for (int c = j; c < n_chunks; c += kMergeLanes) {
+  for (int c = j; c < n_chunks; c += L) {
     const float2 v = part[((int64_t)c * G + g) * rows + rr];
     t1 += v.x;
     s += v.y;
   }
-  t1 = merge_sum(t1);
-  s = merge_sum(s);
+  t1 = merge_sum<double, L>(t1);
+  s = merge_sum<double, L>(s);
   if (j == 0 && r < rows) kl[(int64_t)g * rows + r] = (float)(t1 + log1p(s));
 }
 
@@ -370,7 +371,13 @@ hipError_t launch_lm_kl(const bf16_t* xc, const bf16_t* xp, int64_t pass_stride,
     return hipErrorInvalidValue;
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  kl_merge_kernel<<<dim3((rows + kMergeRows - 1) / kMergeRows, G), 256, 0, s>>>(part, chunks, G, rows, kl);
+  // up to 16 chunks (many rows): a thread per row, whose loads are whole lines of neighbouring rows
+  // (12 passes of 16384 rows, 16 chunks: 10 us against 19 with 16 lanes; 32768 rows, 8 chunks 8
+  // against 36)
+  if (chunks <= kMergeLanes)
+    kl_merge_kernel<1><<<dim3((rows + 255) / 256, G), 256, 0, s>>>(part, chunks, G, rows, kl);
+  else
+    kl_merge_kernel<kMergeLanes><<<dim3((rows + kMergeRows - 1) / kMergeRows, G), 256, 0, s>>>(part, chunks, G, rows, kl);
   return hipGetLastError();
 }
 
