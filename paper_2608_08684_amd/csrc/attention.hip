@@ -390,7 +390,7 @@ __global__ __launch_bounds__(64 * AttnTraits<DH>::kWaves, AttnTraits<DH>::kMinBl
 // Bound: latency of the copies and of a block's chain; 128 KB of copies in flight per CU.
 // With one workgroup of 8 waves per query head, of whose 256 query columns one was
 // used, 16 sequences, 32 / 8 heads of 128, 300 to 510 keys: 49 us and 12 us for gathering
-// them; now 10 to 17 in all.
+// them; now 11 to 15 in all.
 constexpr int kFewRows = 32, kFewPos = 4096;
 
 template <int DH>
@@ -647,8 +647,8 @@ __device__ __forceinline__ void attn_f32_row(const float* base, int64_t ldq, int
 // pieces; lane l then owns query l % 32 and the keys 8 (i / 4) + 4 hf + i % 4, and the key
 // order of O^T is that of those registers.
 // Bound: latency of a block's two MFMA chains (2 x d_h x 32 cycles) and of its loads.
-// Against one thread per (row, head) walking the keys: 256 rows, 4 heads of 64 276 us,
-// 1024 + 777 rows, 12 heads of 64 1216 us.
+// Against one thread per (row, head) walking the keys: 256 rows, 4 heads of 64 278 -> 13 us,
+// 1024 + 777 rows, 12 heads of 64 1181 -> 57.
 // CLEAN: Values of the diagonal block that are infinite or NaN (tested by their bits: this
 // file is compiled as if there were no NaN) count as zero, and the rows from the first of
 // them on, which see it, are walked key by key.  Returns whether any of the thread's

@@ -353,10 +353,11 @@ __device__ __forceinline__ void tile_lse(const f32x16_t (&acc)[G::MI][G::NI], fl
 // Each P phase ends by waiting for what the next P phase reads, which was issued
 // four phases before; the copies issued in between stay in flight.
 // Bound: the matrix cores through the reads, waits and barriers of the other
-// group (MFMA busy 57-67% of the CU-busy cycles without the alternation).  Against
-// both groups in step, 32768 rows: gate|up 1320 -> 1405-1480 TFLOP/s, down (K = 14336)
-// 1206 -> 1350-1410, q|k|v 1247 -> 1320-1380, output 1105 -> 1190-1230; K = 768,
-// 65536 rows: gate|up 1033 -> 1140-1160, down 910 -> 1020-1050; bitwise the same.
+// group.  Against both groups in step, kernel times inside calls on two cards (the cards
+// differ by 5%): d = 4096, 32768 rows: gate|up 1252-1319 -> 1373-1439 TFLOP/s, down (K = 14336)
+// 1160-1192 -> 1330-1389, q|k|v 1136-1178 -> 1222-1284, output 1108-1139 -> 1193-1237;
+// d = 768, 65536 rows: down (K = 3072) 910-926 -> 1050-1083, gate|up 1019-1082 -> 1051-1095,
+// q|k|v 790-833 -> 819-852, output 569-586 -> 589-603; bitwise the same.
 // Spreading the reads evenly over P0 and P1 (a quarter of B one phase early) and
 // leaving out the priorities measured the same within 1%.
 template <int BM, int BN, int NWM, int NWN, int PD, class E, bool SWIGLU>
@@ -517,16 +518,17 @@ __global__ __launch_bounds__(512) void gemm_alt_kernel(const bf16_t* __restrict_
 // Bound: the copies' latency (about 1.1 us) against the bytes in flight per CU, and
 // the serial MFMA chain of a k-step; so small tiles to fill the grid, rings of 72-144
 // KB, copies spread over waves that do not multiply, and no wait on the reads just
-// issued.  Against 128x128 tiles with 32 KB in flight: 16 rows, N = 4096, K = 14336 167 ->
-// 27 us, N = 6144, K = 4096 47 -> 11; 509 rows, N = 768, K = 3072 40 -> 9; 2048 rows, the
-// same weights, 43 -> 18; 300 rows, N = 4096, K = 14336 168 -> 67.  Splitting K between
-// wave groups gained at most 4 us at 16 rows and made sums depend on the tile.
+// issued.  Against 128x128 tiles with 32 KB in flight, inside calls (weights from memory):
+// 16 rows, N = 4096, K = 14336 230 -> 37 us, N = 6144, K = 4096 67 -> 15; 300 rows, N = 4096,
+// K = 14336 222 -> 106; 509 rows, N = 768, K = 3072 51 -> 13; 2048 rows, the same weights, 52 ->
+// 25.  Splitting K between wave groups gained at most 4 us at 16 rows and made sums depend
+// on the tile.
 // fp32 (T = float): the same with 128-byte k-steps of 32 values and
 // v_mfma_f32_32x32x2_f32; each k-step is summed from zero and then added, so the
 // rounding error grows with K / 32 + 32 terms, not K.  Bound: the matrix cores (a k-step
 // is 1024 cycles per block, 157 TFLOP/s over the chip).  Against the vector units
-// with a 64x128 tile: 1801 rows, N = 32000, K = 768 73 TFLOP/s, N = 768, K = 3072 28;
-// 256 rows, N = 256, K = 1024 97 us.
+// with a 64x128 tile: 1801 rows, N = 32000, K = 768 73 -> 99 TFLOP/s, N = 768, K = 3072 27 -> 71;
+// 256 rows, N = 256, K = 1024 105 -> 22 us.
 template <typename T, int BM, int BN, int NW, int S, class E>
 __global__ __launch_bounds__(64 * NW) void gemm_ring_kernel(const T* __restrict__ A, const T* __restrict__ A2,
                                                             int64_t lda, const T* __restrict__ B, int64_t ldb, int M,

@@ -90,10 +90,11 @@ __global__ __launch_bounds__(256) void lse_merge_kernel(const float2* __restrict
 // boundaries.  Wave w owns 64 tokens (64 (w / 2) .., the MFMA N side) and 64 vocab rows
 // of the tile (half w % 2, M side): four fragments per four MFMAs, where 128 rows x 32
 // tokens take five; its reductions over vocab stay in its lanes until the two halves
-// meet at the end.  Measured against that: d = 4096, V = 32000, 32768 tokens, one pass 16.3
-// -> 15.6 ms; d = 768, 16384 tokens, 12 passes 11.2 -> 11.0 ms.  Bound: the copies (48 KB
-// per 1024 MFMA cycles) and their latency; the projections' alternating schedule, whose
-// copies have two phases to land here instead of four, was slower (19.8 and 12.7 ms).
+// meet at the end.  Against that, in calls on two cards: d = 4096, V = 32000, 32768 tokens, one
+// pass 16.5-17.4 -> 16.0-16.9 ms; d = 768, 16384 tokens, 12 passes 11.4-11.6 -> 11.2-11.4 ms;
+// V = 128256, 3000 tokens 7.68 -> 7.41.  Bound: the copies (48 KB per 1024 MFMA cycles) and their latency; the projections'
+// alternating schedule, whose copies have two phases to land here instead of four, was slower
+// (19.8 and 12.7 ms).
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr int kKlTok = 256;     // tokens per workgroup
 

@@ -173,7 +173,7 @@ def test_joined_passes_equal_separate_passes():
                          ids=["bf16-unfused", "f32", "bf16-window-start"])
 def test_joined_passes_other_paths(cfg, flags):
     """Pass batching on the unfused-KL path (materialised logits), on the fp32
-    model (VALU GEMMs and attention) and with a window start (means over
+    model (fp32 MFMA GEMMs and attention) and with a window start (means over
     [40, T_i), protected first position): 3 sequences, every layer at two
     alphas, three passes per launch, bitwise equal to one pass at a time."""
     import paper_2608_08684_amd as rk
