@@ -43,12 +43,12 @@ HBM_PEAK_GBS = 8000.0         # MI355X HBM3E
 # while the family's kernel sources hash to the recorded value, so a changed
 # kernel or launch shape reports null until re-measured.
 TRAFFIC = {
-    ("gemm_gate_up", "gpt2s-bf16", 1): {"bytes_per_launch": 327091576, "fetch_bytes": 226428280,
-                                     "write_bytes": 100663296, "sources": "5138ba9bfc0b0ac1"},
-    ("gemm_gate_up", "llama3-8b-long-bf16", 1): {"bytes_per_launch": 12252797172, "fetch_bytes": 11313273076,
-                                                 "write_bytes": 939524096, "sources": "3637cd35c57e36e6"},
-    ("attention", "llama3-8b-long-bf16", 1): {"bytes_per_launch": 1677633940, "fetch_bytes": 1409141478,
-                                              "write_bytes": 268492462, "sources": "e2f55bc60551caaf"},
+    ("gemm_gate_up", "gpt2s-bf16", 1): {"bytes_per_launch": 327030041, "fetch_bytes": 226366745,
+                                     "write_bytes": 100663296, "sources": "b4ce65146a875efe"},
+    ("gemm_gate_up", "llama3-8b-long-bf16", 1): {"bytes_per_launch": 12352823471, "fetch_bytes": 11413299375,
+                                                 "write_bytes": 939524096, "sources": "b4ce65146a875efe"},
+    ("attention", "llama3-8b-long-bf16", 1): {"bytes_per_launch": 1679060548, "fetch_bytes": 1410540458,
+                                              "write_bytes": 268520090, "sources": "d9214e7bf968905a"},
 }
 FAMILY_SOURCES = {
     "gemm": ["paper_2608_08684_amd/csrc/gemm.hip", "paper_2608_08684_amd/csrc/mfma_tile.h"],

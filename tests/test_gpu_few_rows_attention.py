@@ -194,6 +194,7 @@ def test_few_rows_against_float64(heads, kv_heads, dh, P, W, keep):
     (4, 2, 64, 70, [16, 3, 9]),       # two query heads per KV head: at most 16 rows
     (2, 2, 64, 95, [32, 17]),         # one: at most 32
     (4, 1, 128, 129, [8, 1, 5]),
+    (4, 1, 128, 65, [8, 33, 2]),      # the second one takes the general kernel
 ])
 def test_perturbed_prefix_values(heads, kv_heads, dh, P, windows):
     """Short ragged windows behind perturbed prefix Values: rk_profile_layer against the oracle (tolerances as in the
